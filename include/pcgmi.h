@@ -8,8 +8,10 @@
  * matrix-free (Sec. VI), with the Jacobi preconditioner D = diag(A) applied
  * as element-wise scaling. PCG is composed of the element-wise update
  * (Sec. IV), the global dot-product reduction (Sec. V) and the stencil
- * (Sec. VI); here they are fused into two kernels per iteration, or into one
- * kernel with one grid reduction on small grids (pcg_options.single_reduction).
+ * (Sec. VI). A grid that fits the chip's registers and LDS is solved there, in
+ * one persistent launch for all iterations; otherwise they are fused into two
+ * kernels per iteration, or into one kernel with one grid reduction on small
+ * grids (pcg_options.single_reduction).
  *
  * Conventions for every entry point:
  *  - Grids are contiguous C-order [nz][ny][nx] arrays, x fastest.
@@ -60,7 +62,9 @@ typedef struct {
     int use_x0;        /* 0 (default): x0 = 0; 1: x holds the initial guess on entry */
     int use_graph;     /* 1 (default): replay captured graph chunks; 0: eager launches */
     int kernel_timing; /* 1: eager launches with HIP events around every iteration
-                          kernel; sums are returned in pcg_info */
+                          kernel; sums are returned in pcg_info. On the chip: the
+                          wall-clock time of an iteration's two phases (p, q = A p and
+                          p.q; x, r and r.r), grid sums included */
     int tile_x;        /* stencil tile in x (points); 0 = autotuned default */
     int tile_y;        /* stencil tile in y (rows); 0 = default */
     int zchunk;        /* z planes per work-group; 0 = default */
@@ -76,7 +80,14 @@ typedef struct {
                           iteration (Hestenes-Stiefel PCG); 1 = one fused kernel and one
                           reduction per iteration (Chronopoulos-Gear single-reduction
                           PCG, the same iterates in exact arithmetic; moves 48 instead of
-                          40 bytes per point); -1 = default (chosen by grid size) */
+                          40 bytes per point); -1 = default: on the chip where the grid
+                          fits (F32 or F64 storage, FP64 x accumulator, no tile or zchunk
+                          given; up to about 4 M points in F32, half of that in F64 or with
+                          cell coefficients), else chosen by grid size. On the chip the
+                          iterates are those of 0 (other summation order), use_graph,
+                          chunk_iters and x_defer change nothing, and solves of one process
+                          take turns on a device once their work-groups would exceed its
+                          CUs */
     int zchunk_update;  /* z planes per work-group of the two-kernel form's update kernel
                           when it adds to x (every second iteration with x_defer = 1; the
                           other updates take the direction kernel's plan):

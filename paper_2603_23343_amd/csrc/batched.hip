@@ -32,6 +32,7 @@
 #include <string>
 #include <vector>
 
+#include "resident.hpp"
 #include "trace.hpp"
 #include "zkernel.hpp"
 
@@ -436,6 +437,7 @@ struct BatchImpl {
     int xcd_local = 0;  // problems whose barriers ran XCD-local in the last solve
     int force_agent = 0;  // 1: every group barrier takes the agent-scope fence form
     int max_restarts = BATCH_MAX_RESTARTS;  // FP64-residual restarts per problem
+    int dev = 0, cus = 0;
 };
 
 namespace {
@@ -669,8 +671,14 @@ pcg_status upload_plans(BatchImpl& B) {
     return PCG_OK;
 }
 
+// How long a launch waits for other persistent launches of this process to
+// end (it fills the device, so it holds every CU); it starts anyway when that
+// runs out, and its own barrier bound then decides.
+constexpr double BATCH_HOLD_S = 10.0;
+
 // Run the whole batch eagerly and read back per-problem results.
 pcg_status run_once(BatchImpl& B, const float* b, double* x, double rtol2, int maxit, int* herr) {
+    CuHold hold(B.dev, B.cus, B.cus, BATCH_HOLD_S);
     BCHK(enqueue_batch(B, b, x, rtol2, maxit, B.stream));
     BCHK(hipMemcpyAsync(B.h_out, B.out, sizeof(BatchOut) * B.nprob, hipMemcpyDeviceToHost, B.stream));
     BCHK(hipMemcpyAsync(herr, B.err, sizeof(int), hipMemcpyDeviceToHost, B.stream));
@@ -826,6 +834,8 @@ pcg_status pcg_batch_create(pcg_batch* out, int nprob, const int* dims, const in
             if (*c == '"' || *c == '\\') *c = '_';
         B.device_tag = tag;
     }
+    B.dev = dev;
+    B.cus = prop.multiProcessorCount;
     char msg[256] = {0};
     pcg_status st = batch_layout(B, dims, std::min(cap, 8192), msg, sizeof msg);
     if (st != PCG_OK) {
@@ -967,6 +977,7 @@ pcg_status pcg_batch_solve(pcg_batch bt, const float* b, double* x, double rtol,
     BatchImpl& B = bt->impl;
     const auto t0 = std::chrono::steady_clock::now();
     const double rtol2 = rtol * rtol;
+    CuHold hold(B.dev, B.cus, B.cus, BATCH_HOLD_S);
     if (use_graph) {
         if (!B.graph || B.g_b != b || B.g_x != x || B.g_rtol2 != rtol2 || B.g_maxit != maxit) {
             if (B.graph) {

@@ -1,0 +1,10 @@
+// resident_f32.hip -- instances of the on-chip PCG kernel.
+#include "resident_kernel.hpp"
+
+namespace pcgmi {
+
+hipError_t launch_resident_f32(const ResLaunch& a, hipStream_t s) {
+    return resident::pick_shape<float, double, false>(a, s);
+}
+
+}  // namespace pcgmi

@@ -22,6 +22,7 @@
 #include "internal.hpp"
 #include "ops.hpp"
 #include "pcgmi.h"
+#include "resident.hpp"
 #include "trace.hpp"
 
 using namespace pcgmi;
@@ -121,6 +122,16 @@ struct pcg_ctx_s {
     bool sr_active = false;
     hipEvent_t ev_chunk[2] = {nullptr, nullptr};
     int last_iters = 0;
+    // on-chip form (resident_kernel.hpp): plan for the current operator,
+    // exchange buffers (zeroed once; sums are numbered, never reused)
+    int dev = 0, cus = 0;
+    bool res_ok = false;       // the grid fits and the options leave the form open
+    bool res_timeout = false;  // a launch could not get its work-groups together: not tried again
+    ResPlan res_plan{};
+    void* res_mem = nullptr;  // ResOut (256 bytes), the slots, the surfaces
+    size_t res_bytes = 0;
+    ResOut* hres_out = nullptr;  // pinned, behind hres
+    uint32_t res_next = 1;
     // operator: constant coefficients unless pcg_set_coefficients gave k
     const float* kc = nullptr;  // caller's cell coefficients (device, FP32)
     void* dinv = nullptr;       // inverse Jacobi diagonal (storage type), owned
@@ -182,7 +193,7 @@ void free_ctx(pcg_ctx c) {
     for (auto& e : c->ev_chunk)
         if (e) (void)hipEventDestroy(e);
     void* dev[] = {c->r, c->p[0], c->p[1], c->xacc, c->partials, c->ticket, c->st, c->hist, c->res2, c->rhat,
-                   c->dinv, c->q, c->z, c->sr};
+                   c->dinv, c->q, c->z, c->sr, c->res_mem};
     for (void* d : dev)
         if (d) (void)hipFree(d);
     if (c->hst) (void)hipHostFree(c->hst);
@@ -383,12 +394,81 @@ bool want_single_reduction(pcg_ctx c) {
     return (c->dt == DT_F32 || c->dt == DT_F64) && c->n <= ((int64_t)1 << 17);
 }
 
+// Whether solves of this context may run on the chip: the caller left the
+// iteration form and the tiles to the library, the types are compiled, and
+// the grid fits. The two-kernel form moves 34 bytes per point and iteration
+// through HBM and waits for two kernel boundaries; on the chip an iteration
+// took 3.7 us against 11.5-15 at 32^3, 9.3 against 21 at 128^3, 12 against 29
+// on 512 x 112 x 64, 9.3 against 40 at 128^3 with cell coefficients and 11.6
+// against 41 at 128^3 in FP64, so it is taken wherever it fits (about 4.1 M
+// FP32 points, half as many in FP64 or with coefficients). Without the
+// workspace the other forms serve.
+void plan_resident(pcg_ctx c) {
+    c->res_ok = false;
+    const pcg_options& o = c->opt;
+    if (o.single_reduction >= 0 || o.tile_x > 0 || o.tile_y > 0 || o.zchunk > 0 || o.zchunk_update != 0) return;
+    if ((c->dt != DT_F32 && c->dt != DT_F64) || o.x_accum != DT_F64) return;
+    if (!resident_plan(c->nx, c->ny, c->nz, c->dt, c->kc != nullptr, c->cus, &c->res_plan)) return;
+    const size_t need = RES_HEAD_BYTES + RES_SLOT_BYTES +
+                        (size_t)2 * c->res_plan.geo.G * c->res_plan.S * (c->dt == DT_F64 ? 8 : 4);
+    if (need > c->res_bytes) {
+        if (c->res_mem) (void)hipFree(c->res_mem);
+        c->res_bytes = 0;
+        if (hipMalloc(&c->res_mem, need) != hipSuccess) {
+            c->res_mem = nullptr;
+            return;
+        }
+        if (launch_zero(DT_F64, (RES_HEAD_BYTES + RES_SLOT_BYTES) / 8, c->res_mem, c->stream) != hipSuccess) return;
+        c->res_bytes = need;
+    }
+    c->res_ok = true;
+}
+
+// Run a started solve to its end on the chip. *ran is false when its
+// work-groups could not be brought together: the vectors may then hold a mix
+// of the start and the end of the solve, and the caller starts over.
+pcg_status run_resident(pcg_ctx c, SolveState* fin, IterResult* out, bool* ran) {
+    *ran = false;
+    CuHold hold(c->dev, c->res_plan.geo.G, c->cus, 2.0);
+    if (!hold.ok()) return PCG_OK;
+    hipStream_t st = c->stream;
+    char* const mem = static_cast<char*>(c->res_mem);
+    ResLaunch a{};
+    a.plan = c->res_plan;
+    a.r = c->r;
+    a.x = c->xacc;
+    a.kc = c->kc;
+    a.dinv = op_of(c).dinv;
+    a.st = c->st;
+    a.hist = c->hist;
+    a.slots = mem + RES_HEAD_BYTES;
+    a.surf = mem + RES_HEAD_BYTES + RES_SLOT_BYTES;
+    a.base = c->res_next;
+    a.out = reinterpret_cast<ResOut*>(mem);
+    a.timing = c->opt.kernel_timing;
+    HIPCHK(launch_pcg_resident(c->dt, c->opt.x_accum, a, st));
+    HIPCHK(hipMemcpyAsync(&c->hst[1], c->st, sizeof(SolveState), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipMemcpyAsync(c->hres_out, mem, sizeof(ResOut), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
+    if (c->hres_out->timeout) {
+        c->res_timeout = true;
+        return PCG_OK;
+    }
+    *fin = c->hst[1];
+    c->res_next += (uint32_t)fin->iters + 2;
+    out->k1_ms = 1e-5 * (double)c->hres_out->ticks1;
+    out->k2_ms = 1e-5 * (double)c->hres_out->ticks2;
+    out->nk = fin->iters;
+    *ran = true;
+    return PCG_OK;
+}
+
 // Start a solve of A x = b on the workspace (x0 = 0, or x0 given in x0 of
 // type x0_dt) and run PCG iterations until the device state says done:
 // converged, breakdown, maxit, or (stag > 0) no 10% improvement of the best
 // residual for stag iterations. The iterate is left in c->xacc.
 pcg_status run_iterations(pcg_ctx c, const void* b, const void* x0, int x0_dt, double rtol, int maxit, int stag,
-                          IterResult* out) {
+                          IterResult* out, bool allow_resident = true) {
     pcg_status s = ensure_hist(c, maxit);
     if (s != PCG_OK) return s;
     hipStream_t st = c->stream;
@@ -411,6 +491,15 @@ pcg_status run_iterations(pcg_ctx c, const void* b, const void* x0, int x0_dt, d
     } else {
         HIPCHK(launch_pcg_start_zero(c->dt, c->n, b, c->r, c->xacc, xacc_dt, c->p[0], op_of(c).dinv, c->st,
                                      c->hist, red_of(c), st));
+    }
+    const bool on_chip = allow_resident && c->res_ok && !c->res_timeout;
+    if (on_chip) {
+        bool ran = false;
+        s = run_resident(c, &out->fin, out, &ran);
+        if (s != PCG_OK) return s;
+        if (!ran) return run_iterations(c, b, x0, x0_dt, rtol, maxit, stag, out, false);
+        c->last_iters = out->fin.iters;
+        return PCG_OK;
     }
     c->sr_active = want_single_reduction(c);
     if (c->sr_active) {
@@ -803,7 +892,8 @@ pcg_status pcg_create(pcg_ctx* out, int nx, int ny, int nz, pcg_dtype storage, v
     size_t maxblk = std::max<size_t>({(size_t)c->geo.nblocks, (size_t)c->geo_upd.nblocks, (size_t)c->geo_res.nblocks,
                                       (size_t)DOT_MAX_BLOCKS});
     c->partials_cap = (size_t)MAX_RED_COMPONENTS * maxblk;
-    hipError_t e = hipSuccess;
+    hipError_t e = hipGetDevice(&c->dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->dev);
     if (e == hipSuccess) e = hipMalloc(&c->r, es * n);
     if (e == hipSuccess) e = hipMalloc(&c->p[0], es * n);
     if (e == hipSuccess) e = hipMalloc(&c->p[1], es * n);
@@ -813,13 +903,14 @@ pcg_status pcg_create(pcg_ctx* out, int nx, int ny, int nz, pcg_dtype storage, v
     if (e == hipSuccess) e = hipMalloc(&c->st, 2 * sizeof(SolveState));  // current state and the chain's second
     if (e == hipSuccess) e = hipMalloc(&c->res2, 2 * sizeof(double));
     if (e == hipSuccess) e = hipHostMalloc(&c->hst, 2 * sizeof(SolveState), hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc(&c->hres, 2 * sizeof(double), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc(&c->hres, 2 * sizeof(double) + sizeof(ResOut), hipHostMallocDefault);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_chunk[0], hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_chunk[1], hipEventDisableTiming);
     if (e != hipSuccess) {
         free_ctx(c);
         return fail(e == hipErrorOutOfMemory ? PCG_E_NOMEM : PCG_E_HIP, "pcg_create: %s", hipGetErrorString(e));
     }
+    c->hres_out = reinterpret_cast<ResOut*>(c->hres + 2);
     e = launch_zero(DT_F64, 32, c->ticket, c->stream);  // 256 bytes
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
@@ -831,6 +922,7 @@ pcg_status pcg_create(pcg_ctx* out, int nx, int ny, int nz, pcg_dtype storage, v
         free_ctx(c);
         return s;
     }
+    plan_resident(c);
     *out = c;
     return PCG_OK;
 }
@@ -1404,6 +1496,7 @@ pcg_status pcg_set_coefficients(pcg_ctx c, const float* k_cell) {
     if (!c) return fail(PCG_E_ARG, "pcg_set_coefficients: null context");
     if (!k_cell) {
         c->kc = nullptr;
+        plan_resident(c);
         if (c->chunk) {
             HIPCHK(hipGraphExecDestroy(c->chunk));
             c->chunk = nullptr;
@@ -1417,6 +1510,7 @@ pcg_status pcg_set_coefficients(pcg_ctx c, const float* k_cell) {
     if (!c->dinv) HIPCHK(hipMalloc(&c->dinv, dt_size(c->dt) * c->n));
     HIPCHK(launch_var_dinv(c->dt, c->plan, c->geo, k_cell, c->dinv, c->stream));
     c->kc = k_cell;
+    plan_resident(c);
     if (c->chunk) {  // captured kernels use the old operator
         HIPCHK(hipGraphExecDestroy(c->chunk));
         c->chunk = nullptr;
