@@ -397,20 +397,26 @@ pcg_status pcg_make_pairs(pcg_ctx ctx, int npairs, const double *r_snaps, const 
  * x0 = 0) in ONE persistent kernel launch. Batching is not part of the
  * paper's method; the per-problem iteration is the single-problem solver's.
  *
- * Every work-group of the launch belongs to one problem; a problem's
- * work-groups form a group on one XCD that meets at group barriers twice per
- * iteration. The kernel reads each work-group's XCD from the hardware and,
- * when a group is really on one XCD, synchronises it through that XCD's L2
- * without agent-scope fences. The grid is the device's resident capacity (occupancy query), so
- * all groups run concurrently. Each problem is laid out contiguously, C-order
- * [nz][ny][nx], at its offset in two caller-owned DEVICE arenas: b (FP32) and
- * x (FP64), each of `total` elements (pcg_batch_layout).
+ * Two forms. On the chip (cfgs = NULL, every problem at most about 4 M
+ * points): a problem's vectors live in the registers and LDS of its
+ * work-groups for all its iterations, as in pcg_solve, and work-groups take
+ * problems from lists made at creation. Streaming (otherwise): every
+ * work-group of the launch belongs to one problem; a problem's work-groups
+ * form a group on one XCD that meets at group barriers twice per iteration.
+ * The kernel reads each work-group's XCD from the hardware and, when a group
+ * is really on one XCD, synchronises it through that XCD's L2 without
+ * agent-scope fences. The grid is the device's resident capacity (occupancy
+ * query), so all groups run concurrently. In either form each problem is laid
+ * out contiguously, C-order [nz][ny][nx], at its offset in two caller-owned
+ * DEVICE arenas: b (FP32) and x (FP64), each of `total` elements
+ * (pcg_batch_layout). A batch launch waits for other launches of this process
+ * that need their work-groups together (pcg_solve on the chip, other batches).
  *
- * Internally every problem's r, p and x live in arenas whose rows are padded
+ * In the streaming form every problem's r, p and x live in arenas whose rows are padded
  * to a multiple of 4 points (padding held at 0), so 4-wide vector tiles work
  * for any nx; b is read from and x written to the caller's layout.
  *
- * Tile plans: per problem a work-group tile shape (cfg 0: 64x16 points,
+ * Tile plans (of the streaming form): per problem a work-group tile shape (cfg 0: 64x16 points,
  * 1: 128x8, 2: 256x4, all 4-wide FP32 vectors; 5: 64x4 scalar) and a
  * z-chunk. The z-chunk follows from the shape and the
  * group size (fewest planes for the busiest work-group). The shape is given
@@ -436,17 +442,19 @@ pcg_status pcg_batch_destroy(pcg_batch batch);
 
 /* Host outputs, each optional (NULL): offsets int64[nprob] (element offset of
  * each problem in the arenas, a multiple of 64), total (arena length),
- * plans int[nprob][4] {cfg, zc, work-groups, tiles}, grid int[3]
- * {work-groups of the launch, problems whose shape was measured, problems
- * whose group barriers ran in the XCD-local form in the last solve (all of
- * them when every work-group ran on the XCD the layout assigns it; otherwise
- * those groups use agent-scope fences)}. */
+ * plans int[nprob][4] {cfg, zc, work-groups, tiles} of the streaming form, grid
+ * int[3] {work-groups of its launch, problems whose shape was measured,
+ * problems that used no agent-scope fences in the last solve: those on the
+ * chip, and those whose group barriers ran in the XCD-local form (all of them
+ * when every work-group ran on the XCD the layout assigns it)}. */
 pcg_status pcg_batch_layout(pcg_batch batch, int64_t *offsets, int64_t *total, int *plans, int *grid);
 
 /* Group-barrier form of later solves: 0 (default) = XCD-local where a group's
  * work-groups all run on one XCD, agent-scope fences otherwise; 1 = agent-scope
  * release / acquire fences for every group (the general form, slower; the
- * same arithmetic, so the same results). PCG_E_ARG for another value. */
+ * same arithmetic, so the same results). On the chip both are the same (the
+ * sums there need neither) and form 1 only clears the count that
+ * pcg_batch_layout reports. PCG_E_ARG for another value. */
 pcg_status pcg_batch_set_barrier(pcg_batch batch, int form);
 
 /* FP64-residual restarts per problem in later solves: 0 = never (each
@@ -458,9 +466,9 @@ pcg_status pcg_batch_set_restarts(pcg_batch batch, int max_restarts);
  * recursion stops, its FP64 true residual b - A x is computed; if that is
  * still above rtol ||b_i||, the problem restarts from x with r = fl32(b - A x)
  * and beta = 0 (at most 3 times, pcg_batch_set_restarts), as pcg_solve does. b: DEVICE FP32 arena
- * (read only); x: DEVICE FP64 arena (written). use_graph = 1 captures
- * [barrier reset, persistent kernel] in a HIP graph on the first call and
- * replays it while (b, x, rtol, maxit) stay the same. Host outputs (NULL to
+ * (read only); x: DEVICE FP64 arena (written). use_graph = 1 (streaming form)
+ * captures [barrier reset, persistent kernel] in a HIP graph on the first call
+ * and replays it while (b, x, rtol, maxit) stay the same. Host outputs (NULL to
  * skip): iters int[nprob] (restarts included), relres double[nprob] (FP64
  * ||b - A x|| / ||b||), latency_s double[nprob] (device wall clock from the
  * earliest problem's start to this problem's end), restarts int[nprob],

@@ -32,8 +32,9 @@ bool resident_candidate(int nx, int ny, int nz, int dt, bool var, int lx, int ly
     const int zr = TZ * V, zp = (zr + 3) & ~3;
     p.S = 2 * (TY * zp + TX * zp + TX * TY);
     if ((int64_t)nx * ny * nz > (int64_t)1 << 27) return false;  // 32-bit byte offsets
-    const size_t lds = cs * (((size_t)(TX + 2) * (TY + 2) * (zp + 2) + 1) & ~(size_t)1) + (var ? (size_t)8 * 512 * V : 0);
+    const size_t lds = cs * (((size_t)(TX + 2) * (TY + 2) * (zp + 2) + 1) & ~(size_t)1) + (var ? (size_t)8 * 512 * V : 0) + RES_HALO_LDS;
     if (lds > RES_MAX_LDS) return false;
+    p.lds = lds;
     *out = p;
     return true;
 }
@@ -64,11 +65,11 @@ bool resident_plan(int nx, int ny, int nz, int dt, bool var, int max_wg, ResPlan
     return have;
 }
 
-hipError_t launch_pcg_resident(int dt, int xdt, const ResLaunch& a, hipStream_t s) {
-    if (a.plan.geo.G < 1 || a.plan.geo.G > RES_MAX_WG || xdt != DT_F64) return hipErrorInvalidValue;
+hipError_t launch_pcg_resident(int dt, int xdt, const ResPlan& p, const ResTask& a, hipStream_t s) {
+    if (p.geo.G < 1 || p.geo.G > RES_MAX_WG || xdt != DT_F64) return hipErrorInvalidValue;
     const bool var = a.kc != nullptr;
-    if (dt == DT_F32) return var ? launch_resident_f32_var(a, s) : launch_resident_f32(a, s);
-    if (dt == DT_F64) return launch_resident_f64(a, s);
+    if (dt == DT_F32) return var ? launch_resident_f32_var(p, a, s) : launch_resident_f32(p, a, s);
+    if (dt == DT_F64) return launch_resident_f64(p, a, s);
     return hipErrorInvalidValue;
 }
 

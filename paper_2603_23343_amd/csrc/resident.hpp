@@ -10,6 +10,8 @@ namespace pcgmi {
 constexpr int RES_MAX_WG = 256;                    // one work-group per CU
 constexpr size_t RES_MAX_LDS = (size_t)156 << 10;  // of a CU's 160 KiB
 
+constexpr size_t RES_HALO_LDS = (size_t)4 * 512 * 4;  // grid indices of the halo groups
+
 // Compiled work-group shapes (log2 of the threads along x and y; 512 in all)
 // and z points per thread.
 constexpr int RES_SHAPES[][2] = {{5, 4}, {4, 4}, {3, 4}};
@@ -29,7 +31,7 @@ template <int LX, int LY, int V> struct ResShape {
     static constexpr int NXF = TY * ZP, NYF = TX * ZP, NZF = TX * TY;
     static constexpr int S = 2 * (NXF + NYF + NZF);
     static constexpr size_t lds(size_t cs, bool var) {
-        return cs * (((size_t)PP * (ZP + 2) + 1) & ~(size_t)1) + (var ? (size_t)8 * 512 * V : 0);
+        return cs * (((size_t)PP * (ZP + 2) + 1) & ~(size_t)1) + (var ? (size_t)8 * 512 * V : 0) + RES_HALO_LDS;
     }
 };
 
@@ -47,40 +49,79 @@ struct ResPlan {
     ResGeo geo;
     int V;  // z points per thread
     int S;  // values of a box's surface
+    size_t lds;  // dynamic LDS
 };
 
+// Result of a launch (work-group 0), all but the first field.
 struct ResOut {
-    int timeout;  // a wait ran out: the solve did not finish (set once, never cleared)
-    int pad;
-    long long ticks1, ticks2;  // wall-clock ticks (10 ns) of the two phases
+    int timeout;     // a wait ran out: the solve did not finish (set once, never cleared)
+    int done;        // as SolveState::done
+    int iters;       // iterations, restarts included
+    int last_iters;  // iterations since the last restart
+    int restarts;
+    uint32_t used;   // numbers of grid sums used
+    double rr, rr0, rr_true;       // recursive ||r||^2, ||b||^2, FP64 ||b - A x||^2 (judge)
+    long long ticks1, ticks2;      // wall-clock ticks (10 ns) of the two phases
+    long long t_begin, t_done;     // wall clock (judge)
 };
 
+// Components of a grid sum at most, and copies of the slots. Each work-group
+// writes its partial to every copy and polls one, so that 256 work-groups do
+// not poll the same 4 KiB: a sum over 256 work-groups takes 2.7 us with 8
+// copies and 3.4 us with one (64 work-groups: 1.65 and 2.1 us).
+constexpr int RES_SUMS = 3, RES_COPIES = 8;
 constexpr size_t RES_HEAD_BYTES = 256;  // ResOut, padded
-// Two sums, eight copies of two components per work-group, 16 bytes each.
-constexpr uint32_t RES_SLOT_BYTES = 2 * 8 * 2 * RES_MAX_WG * 16;
+static_assert(sizeof(ResOut) <= RES_HEAD_BYTES);
+// Slots of a group of G work-groups: two sets, 16 bytes a component, whole
+// 128-byte lines.
+constexpr int res_slot_pitch(int G) { return (G + 7) & ~7; }
+constexpr uint32_t res_slot_bytes(int G) { return 2u * RES_COPIES * RES_SUMS * (uint32_t)res_slot_pitch(G) * 16u; }
+constexpr uint32_t RES_SLOT_BYTES = res_slot_bytes(RES_MAX_WG);
 
-struct ResLaunch {
-    ResPlan plan;
-    const void* r;  // start residual
-    void* x;        // x accumulator (read and written)
+// One solve. judge = 0: a start made by other kernels (r, x, st) is iterated
+// to its end and x and st are left for others. judge = 1: the solve of A x = b
+// from x = 0 (r is b), FP64 judge and restarts included.
+struct ResTask {
+    ResGeo geo;
+    const void* r;
+    void* r2;  // judge: the residual that a restart begins with (a vector of the storage type)
+    void* x;   // the accumulator, or (judge) the caller's FP64 x
     const float* kc;
     const void* dinv;
     SolveState* st;
-    double* hist;
-    void* slots;    // RES_SLOT_BYTES
+    double* hist;   // may be null
+    void* slots;    // res_slot_bytes(G), zeroed once
     void* surf;     // 2 * G * S values of the arithmetic type
-    uint32_t base;  // number of the first grid sum (never used before on these slots)
     ResOut* out;
+    double rtol2;   // judge
+    uint32_t base;  // number of the first grid sum (never used before on these slots)
     int timing;
+    int judge, maxit, max_restarts;
+    long long wait;  // ticks (10 ns) a work-group waits in a grid sum at most
 };
+constexpr long long RES_WAIT_TICKS = 100000000;  // 1 s
+
+// One problem of a batch: its task and its compiled shape.
+struct ResBatchTask {
+    ResTask task;
+    int shape;  // index into RES_SHAPES
+    int V;
+};
+// All problems of a batch in one launch of nwg work-groups: work-group w runs
+// the boxes work[first[w]] .. work[first[w + 1] - 1], {problem, rank}, in
+// this order, which is the same order of problems for all of them.
+hipError_t launch_batch_resident(const ResBatchTask* tasks, const int2* work, const int* first, int nwg, size_t lds,
+                                 hipStream_t s);
+// Points per thread compiled for batches.
+constexpr int RES_BATCH_VS[] = {4, 8, 12, 16, 24, 32};
 
 bool resident_candidate(int nx, int ny, int nz, int dt, bool var, int lx, int ly, int V, int max_wg, ResPlan* out);
 // A plan for the grid on at most max_wg work-groups; false if it does not fit.
 bool resident_plan(int nx, int ny, int nz, int dt, bool var, int max_wg, ResPlan* out);
-hipError_t launch_pcg_resident(int dt, int xdt, const ResLaunch& a, hipStream_t s);
-hipError_t launch_resident_f32(const ResLaunch& a, hipStream_t s);
-hipError_t launch_resident_f32_var(const ResLaunch& a, hipStream_t s);
-hipError_t launch_resident_f64(const ResLaunch& a, hipStream_t s);
+hipError_t launch_pcg_resident(int dt, int xdt, const ResPlan& p, const ResTask& a, hipStream_t s);
+hipError_t launch_resident_f32(const ResPlan& p, const ResTask& a, hipStream_t s);
+hipError_t launch_resident_f32_var(const ResPlan& p, const ResTask& a, hipStream_t s);
+hipError_t launch_resident_f64(const ResPlan& p, const ResTask& a, hipStream_t s);
 
 // A claim on CUs of a device for the time of a persistent launch: its
 // work-groups wait for each other, so two such launches of this process may

@@ -3,8 +3,8 @@
 
 namespace pcgmi {
 
-hipError_t launch_resident_f32(const ResLaunch& a, hipStream_t s) {
-    return resident::pick_shape<float, double, false>(a, s);
+hipError_t launch_resident_f32(const ResPlan& p, const ResTask& a, hipStream_t s) {
+    return resident::pick_shape<float, double, false>(p, a, s);
 }
 
 }  // namespace pcgmi

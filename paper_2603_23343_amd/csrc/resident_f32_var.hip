@@ -3,8 +3,8 @@
 
 namespace pcgmi {
 
-hipError_t launch_resident_f32_var(const ResLaunch& a, hipStream_t s) {
-    return resident::pick_shape<float, double, true>(a, s);
+hipError_t launch_resident_f32_var(const ResPlan& p, const ResTask& a, hipStream_t s) {
+    return resident::pick_shape<float, double, true>(p, a, s);
 }
 
 }  // namespace pcgmi

@@ -3,8 +3,9 @@
 
 namespace pcgmi {
 
-hipError_t launch_resident_f64(const ResLaunch& a, hipStream_t s) {
-    return a.kc ? resident::pick_shape<double, double, true>(a, s) : resident::pick_shape<double, double, false>(a, s);
+hipError_t launch_resident_f64(const ResPlan& p, const ResTask& a, hipStream_t s) {
+    if (a.kc) return resident::pick_shape<double, double, true>(p, a, s);
+    return resident::pick_shape<double, double, false>(p, a, s);
 }
 
 }  // namespace pcgmi

@@ -38,12 +38,6 @@ namespace resident {
 
 constexpr int RT = 512;     // threads per work-group
 constexpr int RW = RT / 64;  // wavefronts
-// Copies of the slots. Each work-group writes its partial to all of them and
-// polls one, so that 256 work-groups do not poll the same 4 KiB: a sum over
-// 256 work-groups takes 2.7 us with 8 copies and 3.4 us with one (64
-// work-groups: 1.65 and 2.1 us).
-constexpr int RES_COPIES = 8;
-constexpr long long RES_WAIT_TICKS = 100000000;  // 1 s of the 100 MHz wall clock
 constexpr int AGENT = 16;  // cache policy of a buffer access: agent scope (sc1)
 
 using Words4 = __attribute__((ext_vector_type(4))) uint32_t;
@@ -83,37 +77,40 @@ __device__ __forceinline__ double uniform(double v) {
 }
 
 struct SumLds {
-    double wave[2][RW];  // the work-group's wavefront sums
-    double slot[2][RW];  // sums of the slots, per polling wavefront
+    double wave[2][RES_SUMS][RW];  // the work-group's wavefront sums, per set
+    double slot[RES_SUMS][RW];     // sums of the slots, per polling wavefront
     int bad;
 };
 
-// First part of a grid sum: wavefront sums to LDS.
-template <int NC> __device__ __forceinline__ void sum_local(const double (&v)[NC], SumLds& L) {
+// First part of a grid sum: wavefront sums to LDS. Two sets (of LDS and of
+// slots) take turns, so that a work-group may enter the next sum while others
+// still read the last one.
+template <int NC> __device__ __forceinline__ void sum_local(const double (&v)[NC], SumLds& L, int set) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
         const double s = wave_total(v[c]);
-        if ((threadIdx.x & 63) == 63) L.wave[c][threadIdx.x >> 6] = s;
+        if ((threadIdx.x & 63) == 63) L.wave[set][c][threadIdx.x >> 6] = s;
     }
 }
 
-// Slots of one sum: [copy][component][work-group], 16 bytes each.
-__device__ __forceinline__ int slot_at(int copy, int c, int rank) {
-    return ((copy * 2 + c) * RES_MAX_WG + rank) * 16;
+// Slots: [set][copy][component][work-group], 16 bytes each.
+__device__ __forceinline__ int slot_at(int set, int copy, int c, int rank, int G) {
+    return (((set * RES_COPIES + copy) * RES_SUMS + c) * res_slot_pitch(G) + rank) * 16;
 }
 
 // The first threads store the work-group's partial in every copy (after a
 // __syncthreads that follows sum_local).
-template <int NC> __device__ __forceinline__ void sum_publish(SumLds& L, Buf slots, int set, int rank, uint32_t no) {
-    if (threadIdx.x < RES_COPIES) {
+template <int NC>
+__device__ __forceinline__ void sum_publish(SumLds& L, Buf slots, int set, int rank, int G, uint32_t no) {
+    if (G > 1 && threadIdx.x < RES_COPIES) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            double s = L.wave[c][0];
+            double s = L.wave[set][c][0];
 #pragma unroll
-            for (int w = 1; w < RW; ++w) s += L.wave[c][w];
+            for (int w = 1; w < RW; ++w) s += L.wave[set][c][w];
             const uint64_t b = __builtin_bit_cast(uint64_t, s);
             __builtin_amdgcn_raw_buffer_store_b128(Words4{no, (uint32_t)(b >> 32), no, (uint32_t)b}, slots,
-                                                   set + slot_at(threadIdx.x, c, rank), 0, AGENT);
+                                                   slot_at(set, threadIdx.x, c, rank, G), 0, AGENT);
         }
     }
 }
@@ -121,9 +118,18 @@ template <int NC> __device__ __forceinline__ void sum_publish(SumLds& L, Buf slo
 // Last part: wait for all slots and add them; false after a timeout.
 template <int NC>
 __device__ __forceinline__ bool sum_collect(double (&tot)[NC], SumLds& L, Buf slots, int set, int rank, int G,
-                                            uint32_t no) {
+                                            uint32_t no, long long wait) {
     const int t = threadIdx.x, wid = t >> 6;
     const int nw = (G + 63) >> 6;
+    if (G == 1) {  // a lone work-group: its own sums are the totals
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            double s = L.wave[set][c][0];
+            for (int w = 1; w < RW; ++w) s += L.wave[set][c][w];
+            tot[c] = uniform(s);
+        }
+        return true;
+    }
     if (wid < nw) {
         double s[NC];
 #pragma unroll
@@ -136,12 +142,12 @@ __device__ __forceinline__ bool sum_collect(double (&tot)[NC], SumLds& L, Buf sl
                 __asm__ volatile("" ::: "memory");  // the loads stay in the loop
 #pragma unroll
                 for (int c = 0; c < NC; ++c)
-                    a[c] = __builtin_amdgcn_raw_buffer_load_b128(slots, set + slot_at(rank & (RES_COPIES - 1), c, t), 0,
+                    a[c] = __builtin_amdgcn_raw_buffer_load_b128(slots, slot_at(set, rank & (RES_COPIES - 1), c, t, G), 0,
                                                                  AGENT);
 #pragma unroll
                 for (int c = 0; c < NC; ++c) ok = ok && a[c].x == no && a[c].z == no;
                 if (ok) break;
-                if (wall_clock64() - began > RES_WAIT_TICKS) {
+                if (wall_clock64() - began > wait) {
                     L.bad = 1;
                     break;
                 }
@@ -201,23 +207,23 @@ __device__ __forceinline__ void put_one(Buf b, int off, double v) {
 // Element i of an array of T behind a buffer, 0 where ok is false: the offset
 // then lies past the buffer's end, which loads as 0 and stores nothing, so a
 // run of predicated accesses needs no branches.
-template <typename T> __device__ __forceinline__ T get_at(Buf b, int i, bool ok) {
+template <typename T, int POLICY = 0> __device__ __forceinline__ T get_at(Buf b, int i, bool ok) {
     const int off = ok ? i * (int)sizeof(T) : -1;
     if constexpr (sizeof(T) == 8)
-        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(b, off, 0, 0));
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(b, off, 0, POLICY));
     else if constexpr (sizeof(T) == 4)
-        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(b, off, 0, 0));
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(b, off, 0, POLICY));
     else
-        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b16(b, off, 0, 0));
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b16(b, off, 0, POLICY));
 }
-template <typename T> __device__ __forceinline__ void set_at(Buf b, int i, bool ok, T v) {
+template <typename T, int POLICY = 0> __device__ __forceinline__ void set_at(Buf b, int i, bool ok, T v) {
     const int off = ok ? i * (int)sizeof(T) : -1;
     if constexpr (sizeof(T) == 8)
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(Words2, v), b, off, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(Words2, v), b, off, 0, POLICY);
     else if constexpr (sizeof(T) == 4)
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), b, off, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), b, off, 0, POLICY);
     else
-        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), b, off, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), b, off, 0, POLICY);
 }
 
 // Face coefficients of a thread's points (variable operator), computed once.
@@ -226,63 +232,97 @@ template <typename C, int V, bool VAR> struct Faces {
 };
 template <typename C, int V> struct Faces<C, V, false> {};
 
-// T: storage type, X: the x accumulator's type in memory (FP64 registers), V
-// z points per thread, 2^LX x 2^LY threads along x and y (the rest along z).
+// One work-group's part (box `rank`) of a solve. T: storage type, X: the x
+// accumulator's type in memory (FP64 registers), V z points per thread, 2^LX x
+// 2^LY threads along x and y (the rest along z). False when a wait ran out.
 template <typename T, typename X, int V, bool VAR, int LX, int LY>
-__global__ void __launch_bounds__(RT, 2) k_pcg_resident(const ResGeo g, const T* __restrict__ r0, X* __restrict__ xio,
-                                                       const float* __restrict__ kc, const T* __restrict__ dinv_in,
-                                                       SolveState* st, double* hist, void* slots_p, void* surf_p,
-                                                       uint32_t base, ResOut* out, int timing) {
+__device__ __forceinline__ bool solve_box(const ResTask& a, const int rank, unsigned char* dyn, SumLds& L) {
     using C = typename Traits<T>::C;
     using Sh = ResShape<LX, LY, V>;
     constexpr int TX = Sh::TX, TY = Sh::TY, ZR = Sh::ZR, ZP = Sh::ZP, PX = Sh::PX, PP = Sh::PP;
     constexpr int NXF = Sh::NXF, NYF = Sh::NYF, NZF = Sh::NZF, S = Sh::S;
     constexpr int GN = 16 / (int)sizeof(C);            // halo points per group (one 16-byte load)
     constexpr int HG = (S / GN + RT - 1) / RT;         // groups per thread
+    static_assert(HG * RT * sizeof(int) <= RES_HALO_LDS);
     constexpr int NB = VAR ? 2 : 1;
-    extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
-    __shared__ SumLds L;
+    constexpr bool JUDGE = sizeof(X) == 8;
+    const ResGeo& g = a.geo;
+    const bool judge = JUDGE && a.judge;
+    SolveState* const st = a.st;
+    double* const hist = a.hist;
+    const int G = g.G;
     C* tile = reinterpret_cast<C*>(dyn);               // [ZP + 2][TY + 2][TX + 2]
     double* xlds = reinterpret_cast<double*>(tile + ((PP * (ZP + 2) + 1) & ~1));  // [V][RT] (VAR)
+    int* hgi = reinterpret_cast<int*>(xlds + (VAR ? V * RT : 0));  // [HG][RT]
 
-    if (st->done != 0 || st->maxit <= 0) return;  // the same in every work-group
-    const double rr0 = uniform(st->rr0), tol2 = uniform(st->tol2), dconst = uniform(st->dinv);
-    const int maxit = st->maxit, stag = st->stag;
-    double rho = uniform(st->rho), beta_d = uniform(st->beta), rr = uniform(st->rr);
-    double stag_best = uniform(st->stag_best);
-    int iters = st->iters, done = 0, stag_at = st->stag_at;
+    // Scalars of the recursion: from the solve state when the start was made
+    // by other kernels, else (judge) formed here from b.
+    double rr0 = 0.0, tol2 = 0.0, dconst = 1.0 / 6.0, rho = 0.0, beta_d = 0.0, rr = 0.0, stag_best = 0.0;
+    int maxit = a.maxit, stag = 0, iters = 0, done = 0, stag_at = 0;
+    if (!judge) {
+        if (st->done != 0 || st->maxit <= 0) return true;  // the same in every work-group
+        rr0 = uniform(st->rr0);
+        tol2 = uniform(st->tol2);
+        dconst = uniform(st->dinv);
+        maxit = st->maxit;
+        stag = st->stag;
+        rho = uniform(st->rho);
+        beta_d = uniform(st->beta);
+        rr = uniform(st->rr);
+        stag_best = uniform(st->stag_best);
+        iters = st->iters;
+        stag_at = st->stag_at;
+    }
+    const int first = iters;
+    const long long t_begin = judge ? wall_clock64() : 0;
     double sigma = 0.0, alpha_d64 = 0.0;
 
     const int t = threadIdx.x;
     const int tx = t & (TX - 1), ty = (t >> LX) & (TY - 1), tz = t >> (LX + LY);
-    const int rank = (int)xcd_remap(blockIdx.x, gridDim.x);
     const int cx = rank % g.gx, cy = (rank / g.gx) % g.gy, cz = rank / (g.gx * g.gy);
     const int ox = cx * g.bx, oy = cy * g.by, oz = cz * g.bz;
     const int ex = min(g.bx, g.nx - ox), ey = min(g.by, g.ny - oy), ez = min(g.bz, g.nz - oz);
     const int z0 = tz * V;
     const bool act = tx < ex && ty < ey && z0 < ez;
     const int nv = act ? min(V, ez - z0) : 0;
-    const bool full = __syncthreads_and(nv == V) != 0;  // no masking needed in this box
+    const bool full = __syncthreads_and(nv == V) != 0;  // no masking needed in this box (also: LDS is free)
+    // The thread's first point in the grid, its index and its number of points,
+    // formed anew where memory is accessed: offsets and masks kept from the
+    // start, or hoisted, would take registers from the iteration.
+    struct Own {
+        int x, y, z, gi, nv;
+    };
+    auto own = [&]() {
+        int u = threadIdx.x;
+        __asm__ volatile("" : "+v"(u));
+        const int ux = u & (TX - 1), uy = (u >> LX) & (TY - 1), uz = (u >> (LX + LY)) * V;
+        Own o{ox + ux, oy + uy, oz + uz, 0, 0};
+        o.gi = (o.z * g.ny + o.y) * g.nx + o.x;
+        o.nv = ux < ex && uy < ey && uz < ez ? min(V, ez - uz) : 0;
+        return o;
+    };
     const int lb = (z0 + 1) * PP + (ty + 1) * PX + tx + 1;
     // the cell above the thread's last point (the top halo is the tile's last plane)
     const int zt = z0 + nv == ez ? (ZP + 1) * PP + (ty + 1) * PX + tx + 1 : lb + V * PP;
     const bool hxl = cx > 0, hxr = cx + 1 < g.gx, hyl = cy > 0, hyr = cy + 1 < g.gy, hzl = cz > 0, hzr = cz + 1 < g.gz;
     const uint32_t half = (uint32_t)g.G * S * (uint32_t)sizeof(C);
-    const Buf slots = make_buf(slots_p, RES_SLOT_BYTES);
-    const Buf surf = make_buf(surf_p, 2 * half);
+    const Buf slots = make_buf(a.slots, res_slot_bytes(G));
+    const Buf surf = make_buf(a.surf, 2 * half);
     // the grid's arrays (resident_plan keeps them below 2 GiB)
     const uint32_t npts = (uint32_t)g.nx * g.ny * g.nz;
-    const Buf rbuf = make_buf(const_cast<T*>(r0), npts * (uint32_t)sizeof(T));
-    const Buf xbuf = make_buf(xio, npts * (uint32_t)sizeof(X));
-    const Buf dbuf = make_buf(const_cast<T*>(dinv_in), VAR ? npts * (uint32_t)sizeof(T) : 0u);
-    const Buf kbuf = make_buf(const_cast<float*>(kc), VAR ? npts * 4u : 0u);
+    const Buf bbuf = make_buf(const_cast<void*>(a.r), npts * (uint32_t)sizeof(T));
+    const Buf r2buf = make_buf(a.r2, judge ? npts * (uint32_t)sizeof(T) : 0u);
+    const Buf xbuf = make_buf(a.x, npts * (uint32_t)sizeof(X));
+    const Buf dbuf = make_buf(const_cast<void*>(a.dinv), VAR ? npts * (uint32_t)sizeof(T) : 0u);
+    const Buf kbuf = make_buf(const_cast<float*>(a.kc), VAR ? npts * 4u : 0u);
 
     for (int i = t; i < PP * (ZP + 2); i += RT) tile[i] = C(0);
     if (t == 0) L.bad = 0;
 
     // Halo groups of this thread: GN points along z (x and y faces) or along
     // x (z faces). hl: tile index of the first (-1: none), hz: its step; hs:
-    // byte offset of the neighbour's values; rh: the points' residuals.
+    // byte offset of the neighbour's values; hgi: the first point's index in the
+    // grid (LDS); rh: the points' residuals.
     // Points of a group outside the box are carried along in halo cells that
     // no point reads (the tile has ZP + 2 planes).
     int hl[HG], hs[HG], hz[HG];
@@ -301,7 +341,7 @@ __global__ void __launch_bounds__(RT, 2) k_pcg_resident(const ResGeo g, const T*
         if (j >= S) continue;
         int x, y, z, from, face;  // box coordinates of the first point, neighbour's rank and face
         bool ok;
-        int sx = 0, sz = 1;
+        int sx = 0;
         if (j < 2 * NXF) {
             const bool hi = j >= NXF;
             j -= hi ? NXF : 0;
@@ -332,20 +372,16 @@ __global__ void __launch_bounds__(RT, 2) k_pcg_resident(const ResGeo g, const T*
             from = rank + (hi ? g.gx * g.gy : -g.gx * g.gy);
             face = 2 * (NXF + NYF) + (hi ? 0 : NZF);
             sx = 1;
-            sz = 0;
             hz[m] = 1;
         }
         if (ok) {
             hs[m] = (from * S + face + j) * (int)sizeof(C);
             hl[m] = (z == ez ? ZP + 1 : z + 1) * PP + (y + 1) * PX + x + 1;
         }
+        hgi[m * RT + t] = ((oz + z) * g.ny + (oy + y)) * g.nx + ox + x;
+        if constexpr (VAR)
 #pragma unroll
-        for (int e = 0; e < GN; ++e) {
-            const bool in = ok && ((sx && x + e < ex) || (sz && z + e < ez));
-            const int gi = ((oz + z + sz * e) * g.ny + (oy + y)) * g.nx + ox + x + sx * e;
-            rh[m][e] = to_c(get_at<T>(rbuf, gi, in));
-            if constexpr (VAR) dh[m][e] = to_c(get_at<T>(dbuf, gi, in));
-        }
+            for (int e = 0; e < GN; ++e) dh[m][e] = to_c(get_at<T>(dbuf, hgi[m * RT + t] + e * (sx ? 1 : g.nx * g.ny), ok));
     }
 
     // own points
@@ -356,9 +392,8 @@ __global__ void __launch_bounds__(RT, 2) k_pcg_resident(const ResGeo g, const T*
     Faces<C, V, VAR> kf;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-        p[v] = q[v] = C(0);
-        r[v] = to_c(get_at<T>(rbuf, gp + v * gz, v < nv));
-        const double xv = (double)to_c(get_at<X>(xbuf, gp + v * gz, v < nv));
+        p[v] = q[v] = r[v] = C(0);
+        const double xv = (double)to_c(get_at<X>(xbuf, gp + v * gz, v < nv && !judge));
         if constexpr (VAR) {
             xlds[v * RT + t] = xv;
             dv[v] = to_c(get_at<T>(dbuf, gp + v * gz, v < nv));
@@ -389,215 +424,382 @@ __global__ void __launch_bounds__(RT, 2) k_pcg_resident(const ResGeo g, const T*
     }
     __syncthreads();
 
-    uint32_t no = base;
-    long long t1 = 0, t2 = 0, mark = timing ? wall_clock64() : 0;
+    // The box's surface values of q: V values along z per thread on the x and
+    // y faces (16-byte stores), one on the z faces (qt: the thread's topmost).
+    auto publish = [&](const int mine, const C qt) {
+        if (tx == 0 && hxl) put_run<C, V>(surf, mine + (ty * ZP + z0) * (int)sizeof(C), q);
+        if (tx == ex - 1 && hxr) put_run<C, V>(surf, mine + (NXF + ty * ZP + z0) * (int)sizeof(C), q);
+        if (ty == 0 && hyl) put_run<C, V>(surf, mine + (2 * NXF + tx * ZP + z0) * (int)sizeof(C), q);
+        if (ty == ey - 1 && hyr) put_run<C, V>(surf, mine + (2 * NXF + NYF + tx * ZP + z0) * (int)sizeof(C), q);
+        const int zf = mine + (2 * (NXF + NYF) + ty * TX + tx) * (int)sizeof(C);
+        if (z0 == 0 && hzl) put_one(surf, zf, q[0]);
+        if (z0 + nv == ez && hzr) put_one(surf, zf + NZF * (int)sizeof(C), qt);
+    };
+
+    uint32_t no = a.base;
+    bool late = false;  // a wait ran out
+    int restarts = 0, total = 0;
+    double rr_true = 0.0;
     const bool keeper = rank == 0 && t == 0;
-    for (;;) {
-        // ---- direction, q = A p, p.q
-        const C beta = (C)beta_d;
-        const C dc = (C)dconst;
-        if (act) {
+    long long t1 = 0, t2 = 0, mark = a.timing ? wall_clock64() : 0;
+    for (;;) {  // segments: the solve, then its restarts
+        {
+            const Buf rbuf = restarts ? r2buf : bbuf;
+            const Own o = own();
+            int gi = o.gi;
 #pragma unroll
             for (int v = 0; v < V; ++v) {
-                p[v] = stored<T>((VAR ? dv[VAR ? v : 0] : dc) * r[v] + beta * p[v]);
-                tile[lb + v * PP] = p[v];
+                r[v] = to_c(get_at<T, AGENT>(rbuf, gi, v < o.nv));
+                gi += gz;
+                if (v % 8 == 7) __builtin_amdgcn_sched_barrier(0);
             }
+#pragma unroll
+            for (int m = 0; m < HG; ++m)
+#pragma unroll
+                for (int e = 0; e < GN; ++e)
+                    rh[m][e] = to_c(get_at<T, AGENT>(rbuf, hgi[m * RT + t] + e * (hz[m] == 1 ? 1 : gz), hl[m] >= 0));
         }
-#pragma unroll
-        for (int m = 0; m < HG; ++m)
-            if (hl[m] >= 0)
-#pragma unroll
-                for (int e = 0; e < GN; ++e) {
-                    C& c = tile[hl[m] + e * hz[m]];
-                    c = stored<T>((VAR ? dh[VAR ? m : 0][e] : dc) * rh[m][e] + beta * c);
-                }
-        __syncthreads();
-
-        const int mine = (int)((no & 1) * half) + rank * S * (int)sizeof(C);
-        C acc = C(0);
-        if (act) {
-            C qt = C(0);
-            const C below = tile[lb - PP], above = tile[zt];
-            auto sweep = [&]<bool FULL>() {
+        if (judge && restarts == 0) {  // ||b||^2 and r.z of the start r = b
+            double sums[NB];
+            {
+                double s0 = 0.0, s1 = 0.0;
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
-                    const int a = lb + v * PP;
-                    const C b = v == 0 ? below : p[v == 0 ? 0 : v - 1];
-                    C f = v == V - 1 ? above : p[v == V - 1 ? v : v + 1];
-                    if constexpr (!FULL) f = v + 1 == nv ? above : f;
-                    C ax;
-                    if constexpr (VAR)
-                        ax = kf.l[v] * (p[v] - tile[a - 1]) + kf.r[v] * (p[v] - tile[a + 1]) +
-                             kf.d[v] * (p[v] - tile[a - PX]) + kf.u[v] * (p[v] - tile[a + PX]) + kf.z[v] * (p[v] - b) +
-                             kf.z[v + 1] * (p[v] - f);
-                    else
-                        ax = StencilConst<C>::apply(p[v], tile[a - 1], tile[a + 1], tile[a - PX], tile[a + PX], b, f);
-                    if constexpr (!FULL) {
-                        ax = v < nv ? ax : C(0);
-                        qt = v + 1 == nv ? ax : qt;
-                    }
-                    q[v] = ax;
-                    acc += p[v] * ax;
-                    // a few points' LDS reads in flight, not all V of them
-                    if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                    s0 += (double)r[v] * (double)r[v];
+                    if constexpr (VAR) s1 += (double)dv[v] * (double)r[v] * (double)r[v];
                 }
-                if constexpr (FULL) qt = q[V - 1];
-            };
-            if (full) sweep.template operator()<true>();
-            else sweep.template operator()<false>();
-            // the box's surface: V values along z per thread on the x and y
-            // faces (16-byte stores), one on the z faces
-            if (tx == 0 && hxl) put_run<C, V>(surf, mine + (ty * ZP + z0) * (int)sizeof(C), q);
-            if (tx == ex - 1 && hxr) put_run<C, V>(surf, mine + (NXF + ty * ZP + z0) * (int)sizeof(C), q);
-            if (ty == 0 && hyl) put_run<C, V>(surf, mine + (2 * NXF + tx * ZP + z0) * (int)sizeof(C), q);
-            if (ty == ey - 1 && hyr) put_run<C, V>(surf, mine + (2 * NXF + NYF + tx * ZP + z0) * (int)sizeof(C), q);
-            const int zf = mine + (2 * (NXF + NYF) + ty * TX + tx) * (int)sizeof(C);
-            if (z0 == 0 && hzl) put_one(surf, zf, q[0]);
-            if (z0 + nv == ez && hzr) put_one(surf, zf + NZF * (int)sizeof(C), qt);
+                sums[0] = s0;
+                if constexpr (VAR) sums[NB - 1] = s1;
+            }
+            sum_local<NB>(sums, L, 1);
+            __syncthreads();
+            sum_publish<NB>(L, slots, 1, rank, G, no);
+            double tot[NB];
+            late = !sum_collect<NB>(tot, L, slots, 1, rank, G, no, a.wait);
+            ++no;
+            rr0 = rr = tot[0];
+            tol2 = uniform(a.rtol2 * rr0);
+            rho = VAR ? tot[NB - 1] : uniform(dconst * rr0);
+            rr_true = rr0;
+            if (!isfinite(rr0)) done = 2;
+            else if (rr0 == 0.0 || rr <= tol2) done = 1;
+            else if (maxit <= 0) done = 3;
+            if (keeper && hist) hist[0] = rr;
         }
-        {
-            const double v1[1] = {(double)acc};
-            sum_local<1>(v1, L);
-        }
-        __builtin_amdgcn_s_waitcnt(0);  // this wavefront's surface stores have arrived
-        __syncthreads();
-        sum_publish<1>(L, slots, 0, rank, no);
-        double tot1[1];
-        if (!sum_collect<1>(tot1, L, slots, 0, rank, g.G, no)) break;
-        sigma = tot1[0];
-        if (!(sigma > 0.0) || !isfinite(sigma)) {  // as FinAlpha
-            done = 2;
-            break;
-        }
-        alpha_d64 = uniform(rho / sigma);
-        if (timing) {
-            const long long now = wall_clock64();
-            t1 += now - mark;
-            mark = now;
-        }
-
-        // ---- update, r.r
-        Words4 qh[HG];
-        const int theirs = (int)((no & 1) * half);
+        if (late) break;
+        while (!done) {
+            // ---- direction, q = A p, p.q
+            const C beta = (C)beta_d;
+            const C dc = (C)dconst;
+            if (act) {
 #pragma unroll
-        for (int m = 0; m < HG; ++m) {
-            qh[m] = Words4{0, 0, 0, 0};
-            if (hl[m] >= 0) qh[m] = __builtin_amdgcn_raw_buffer_load_b128(surf, theirs + hs[m], 0, AGENT);
-        }
-        const C alpha = (C)alpha_d64;
-        const double alpha_d = (double)alpha;
-        double part[NB];
-        {
-            C a0 = C(0), a1 = C(0);
+                for (int v = 0; v < V; ++v) {
+                    p[v] = stored<T>((VAR ? dv[VAR ? v : 0] : dc) * r[v] + beta * p[v]);
+                    tile[lb + v * PP] = p[v];
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < HG; ++m)
+                if (hl[m] >= 0)
+#pragma unroll
+                    for (int e = 0; e < GN; ++e) {
+                        C& c = tile[hl[m] + e * hz[m]];
+                        c = stored<T>((VAR ? dh[VAR ? m : 0][e] : dc) * rh[m][e] + beta * c);
+                    }
+            __syncthreads();
+
+            C acc = C(0), qt = C(0);
+            if (act) {
+                const C below = tile[lb - PP], above = tile[zt];
+                auto sweep = [&]<bool FULL>() {
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        const int a = lb + v * PP;
+                        const C b = v == 0 ? below : p[v == 0 ? 0 : v - 1];
+                        C f = v == V - 1 ? above : p[v == V - 1 ? v : v + 1];
+                        if constexpr (!FULL) f = v + 1 == nv ? above : f;
+                        C ax;
+                        if constexpr (VAR)
+                            ax = kf.l[v] * (p[v] - tile[a - 1]) + kf.r[v] * (p[v] - tile[a + 1]) +
+                                 kf.d[v] * (p[v] - tile[a - PX]) + kf.u[v] * (p[v] - tile[a + PX]) + kf.z[v] * (p[v] - b) +
+                                 kf.z[v + 1] * (p[v] - f);
+                        else
+                            ax = StencilConst<C>::apply(p[v], tile[a - 1], tile[a + 1], tile[a - PX], tile[a + PX], b, f);
+                        if constexpr (!FULL) {
+                            ax = v < nv ? ax : C(0);
+                            qt = v + 1 == nv ? ax : qt;
+                        }
+                        q[v] = ax;
+                        acc += p[v] * ax;
+                        // a few points' LDS reads in flight, not all V of them
+                        if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if constexpr (FULL) qt = q[V - 1];
+                };
+                if (full) sweep.template operator()<true>();
+                else sweep.template operator()<false>();
+                publish((int)((no & 1) * half) + rank * S * (int)sizeof(C), qt);
+            }
+            {
+                const double v1[1] = {(double)acc};
+                sum_local<1>(v1, L, 0);
+            }
+            __builtin_amdgcn_s_waitcnt(0);  // this wavefront's surface stores have arrived
+            __syncthreads();
+            sum_publish<1>(L, slots, 0, rank, G, no);
+            double tot1[1];
+            if (!sum_collect<1>(tot1, L, slots, 0, rank, G, no, a.wait)) {
+                late = true;
+                break;
+            }
+            sigma = tot1[0];
+            if (!(sigma > 0.0) || !isfinite(sigma)) {  // as FinAlpha
+                done = 2;
+                if (judge) {  // the sets of slots keep taking turns
+                    const double zero[1] = {0.0};
+                    sum_local<1>(zero, L, 1);
+                    __syncthreads();
+                    sum_publish<1>(L, slots, 1, rank, G, no);
+                    late = !sum_collect<1>(tot1, L, slots, 1, rank, G, no, a.wait);
+                }
+                ++no;
+                break;
+            }
+            alpha_d64 = uniform(rho / sigma);
+            if (a.timing) {
+                const long long now = wall_clock64();
+                t1 += now - mark;
+                mark = now;
+            }
+
+            // ---- update, r.r
+            Words4 qh[HG];
+            const int theirs = (int)((no & 1) * half);
+#pragma unroll
+            for (int m = 0; m < HG; ++m) {
+                qh[m] = Words4{0, 0, 0, 0};
+                if (hl[m] >= 0) qh[m] = __builtin_amdgcn_raw_buffer_load_b128(surf, theirs + hs[m], 0, AGENT);
+            }
+            const C alpha = (C)alpha_d64;
+            const double alpha_d = (double)alpha;
+            double part[NB];
+            {
+                C a0 = C(0), a1 = C(0);
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    r[v] = stored<T>(r[v] - alpha * q[v]);
+                    a0 += r[v] * r[v];
+                    if constexpr (VAR) a1 += dv[v] * r[v] * r[v];
+                }
+                part[0] = (double)a0;
+                if constexpr (VAR) part[NB - 1] = (double)a1;
+            }
+            sum_local<NB>(part, L, 1);
+            __syncthreads();
+            sum_publish<NB>(L, slots, 1, rank, G, no);
+            // x and the halo's residual while the partials travel
 #pragma unroll
             for (int v = 0; v < V; ++v) {
-                r[v] = stored<T>(r[v] - alpha * q[v]);
-                a0 += r[v] * r[v];
-                if constexpr (VAR) a1 += dv[v] * r[v] * r[v];
+                if constexpr (VAR) xlds[v * RT + t] += alpha_d * (double)p[v];
+                else x[v] += alpha_d * (double)p[v];
             }
-            part[0] = (double)a0;
-            if constexpr (VAR) part[NB - 1] = (double)a1;
+#pragma unroll
+            for (int m = 0; m < HG; ++m) {
+#pragma unroll
+                for (int e = 0; e < GN; ++e) rh[m][e] = stored<T>(rh[m][e] - alpha * value(qh[m], e, C(0)));
+            }
+            double tot2[NB];
+            if (!sum_collect<NB>(tot2, L, slots, 1, rank, G, no, a.wait)) {
+                late = true;
+                break;
+            }
+            ++no;
+            // as FinBeta; the history holds ||r||^2 until the end of the solve
+            rr = tot2[0];
+            ++iters;
+            if (keeper && hist) hist[iters] = rr;
+            if (a.timing) {
+                const long long now = wall_clock64();
+                t2 += now - mark;
+                mark = now;
+            }
+            if (!isfinite(rr)) done = 2;
+            else if (rr <= tol2) done = 1;
+            else if (iters >= maxit) done = 3;
+            else if (stag > 0) {
+                const double rel = uniform(sqrt(rr / rr0));
+                if (rel < 0.9 * stag_best) {
+                    stag_best = rel;
+                    stag_at = iters;
+                } else if (iters - stag_at >= stag) {
+                    done = 4;
+                }
+            }
+            if (done) break;
+            const double rho_new = VAR ? tot2[NB - 1] : dconst * rr;
+            beta_d = uniform(rho_new / rho);
+            rho = uniform(rho_new);
         }
-        sum_local<NB>(part, L);
+        if (!judge || late) break;
+
+        // ---- the FP64 residual of x, from memory: x goes past the L2s, the
+        // work-groups meet, and a rolled loop (no register arrays) forms r =
+        // b - A x, its norms and the residual a restart begins with.
+        {
+            const Own o = own();
+            int gi = o.gi;
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                double xv;
+                if constexpr (VAR) xv = xlds[v * RT + t];
+                else xv = x[v];
+                set_at<double, AGENT>(xbuf, gi, v < o.nv, xv);
+                gi += gz;
+                if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        {
+            const double zero[1] = {0.0};
+            sum_local<1>(zero, L, 0);
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+            sum_publish<1>(L, slots, 0, rank, G, no);
+            double tot[1];
+            late = !sum_collect<1>(tot, L, slots, 0, rank, G, no, a.wait);
+            if (late) break;
+        }
+        ++no;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        total += iters;
+        constexpr int NS = VAR ? 3 : 2;
+        double sums[NS] = {};
+        {
+            const Own o = own();
+            const int jx = o.x, jy = o.y, jz = o.z;
+            int gi = o.gi;
+#pragma unroll 1
+            for (int v = 0; v < o.nv; ++v) {
+                const double xc = get_at<double>(xbuf, gi, true);
+                auto near = [&](int at, bool ok) { return get_at<double>(xbuf, at, ok); };
+                const bool il = jx > 0, ir = jx + 1 < g.nx, id = jy > 0, iu = jy + 1 < g.ny, ib = jz + v > 0,
+                           ia = jz + v + 1 < g.nz;
+                const double xl = near(gi - 1, il), xr = near(gi + 1, ir), xd = near(gi - g.nx, id),
+                             xu = near(gi + g.nx, iu), xb = near(gi - gz, ib), xa = near(gi + gz, ia);
+                double ax;
+                if constexpr (VAR) {
+                    using K = UK<double>;
+                    auto k = [&](int at, bool ok) { return (double)get_at<float>(kbuf, at, ok); };
+                    ax = StencilVar<double>::apply(K{xc, k(gi, true)}, K{xl, k(gi - 1, il)}, K{xr, k(gi + 1, ir)},
+                                                   K{xd, k(gi - g.nx, id)}, K{xu, k(gi + g.nx, iu)},
+                                                   K{xb, k(gi - gz, ib)}, K{xa, k(gi + gz, ia)});
+                } else {
+                    ax = StencilConst<double>::apply(xc, xl, xr, xd, xu, xb, xa);
+                }
+                const double res = (double)to_c(get_at<T>(bbuf, gi, true)) - ax;
+                const T rs = from_c<T>((C)res);
+                const double rv = (double)to_c(rs);
+                set_at<T, AGENT>(r2buf, gi, true, rs);
+                sums[0] += res * res;
+                sums[1] += rv * rv;
+                if constexpr (VAR) sums[NS - 1] += (double)to_c(get_at<T>(dbuf, gi, true)) * rv * rv;
+                gi += gz;
+            }
+        }
+        sum_local<NS>(sums, L, 1);
+        __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        sum_publish<NB>(L, slots, RES_SLOT_BYTES / 2, rank, no);
-        // x and the halo's residual while the partials travel
+        sum_publish<NS>(L, slots, 1, rank, G, no);
+        double tot[NS];
+        late = !sum_collect<NS>(tot, L, slots, 1, rank, G, no, a.wait);
+        if (late) break;
+        ++no;
+        rr_true = tot[0];
+        if (done != 1 || rr_true <= tol2 || restarts >= a.max_restarts || total >= a.maxit) break;
+        // restart from r = b - A x
+        ++restarts;
+        rr = tot[1];
+        rho = VAR ? tot[NS - 1] : uniform(dconst * rr);
+        beta_d = 0.0;
+        iters = 0;
+        maxit = a.maxit - total;
+        done = !isfinite(rr) ? 2 : rr <= tol2 ? 1 : 0;
+        if (keeper && hist) hist[0] = rr;
+    }
+    if (late) {
+        if (t == 0) __hip_atomic_store(&a.out->timeout, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return false;
+    }
+    if (!judge) {
+        const Own o = own();
+        int ge = o.gi;
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-            if constexpr (VAR) xlds[v * RT + t] += alpha_d * (double)p[v];
-            else x[v] += alpha_d * (double)p[v];
+            double xv;
+            if constexpr (VAR) xv = xlds[v * RT + t];
+            else xv = x[v];
+            set_at<X>(xbuf, ge, v < o.nv, from_c<X>((typename Traits<X>::C)xv));
+            ge += gz;
+            if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
-#pragma unroll
-        for (int m = 0; m < HG; ++m) {
-#pragma unroll
-            for (int e = 0; e < GN; ++e) rh[m][e] = stored<T>(rh[m][e] - alpha * value(qh[m], e, C(0)));
-        }
-        double tot2[NB];
-        if (!sum_collect<NB>(tot2, L, slots, RES_SLOT_BYTES / 2, rank, g.G, no)) break;
-        ++no;
-        // as FinBeta; the history holds ||r||^2 until the end of the solve
-        rr = tot2[0];
-        ++iters;
-        if (keeper && hist) hist[iters] = rr;
-        if (timing) {
-            const long long now = wall_clock64();
-            t2 += now - mark;
-            mark = now;
-        }
-        if (!isfinite(rr)) done = 2;
-        else if (rr <= tol2) done = 1;
-        else if (iters >= maxit) done = 3;
-        else if (stag > 0) {
-            const double rel = uniform(sqrt(rr / rr0));
-            if (rel < 0.9 * stag_best) {
-                stag_best = rel;
-                stag_at = iters;
-            } else if (iters - stag_at >= stag) {
-                done = 4;
-            }
-        }
-        if (done) break;
-        const double rho_new = VAR ? tot2[NB - 1] : dconst * rr;
-        beta_d = uniform(rho_new / rho);
-        rho = uniform(rho_new);
-    }
-    if (L.bad) {
-        if (t == 0) __hip_atomic_store(&out->timeout, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return;
-    }
-    // the offsets are formed again here, not kept in registers since the start
-    int ge = gp;
-    __asm__ volatile("" : "+v"(ge));
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
-        double xv;
-        if constexpr (VAR) xv = xlds[v * RT + t];
-        else xv = x[v];
-        set_at<X>(xbuf, ge, v < nv, from_c<X>((typename Traits<X>::C)xv));
-        ge += gz;
-        if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
     if (rank == 0) {
         __syncthreads();
-        const int first = st->iters;
         if (hist)
-            for (int i = first + 1 + t; i <= iters; i += RT) hist[i] = sqrt(hist[i] / rr0);
-        __syncthreads();
+            for (int i = (judge ? 0 : first + 1) + t; i <= iters; i += RT) hist[i] = rr0 > 0.0 ? sqrt(hist[i] / rr0) : 0.0;
         if (t == 0) {
-            st->rho = rho;
-            st->alpha = alpha_d64;
-            st->beta = beta_d;
-            st->sigma = sigma;
-            st->rr = rr;
-            st->iters = iters;
-            st->done = done;
-            st->stag_at = stag_at;
-            st->stag_best = stag_best;
-            out->ticks1 = t1;
-            out->ticks2 = t2;
+            if (!judge) {
+                st->rho = rho;
+                st->alpha = alpha_d64;
+                st->beta = beta_d;
+                st->sigma = sigma;
+                st->rr = rr;
+                st->iters = iters;
+                st->done = done;
+                st->stag_at = stag_at;
+                st->stag_best = stag_best;
+            }
+            ResOut& o = *a.out;
+            o.done = done;
+            o.iters = judge ? total : iters;
+            o.last_iters = iters;
+            o.restarts = restarts;
+            o.used = no - a.base;
+            o.rr = rr;
+            o.rr0 = rr0;
+            o.rr_true = rr_true;
+            o.ticks1 = t1;
+            o.ticks2 = t2;
+            o.t_begin = t_begin;
+            o.t_done = judge ? wall_clock64() : 0;
         }
     }
+    return true;
 }
 
 template <typename T, typename X, int V, bool VAR, int LX, int LY>
-hipError_t run_resident(const ResLaunch& a, hipStream_t s) {
+__global__ void __launch_bounds__(RT, 2) k_pcg_resident(const ResTask a) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
+    __shared__ SumLds L;
+    solve_box<T, X, V, VAR, LX, LY>(a, (int)xcd_remap(blockIdx.x, gridDim.x), dyn, L);
+}
+
+template <typename T, typename X, int V, bool VAR, int LX, int LY>
+hipError_t run_resident(const ResPlan& p, const ResTask& a, hipStream_t s) {
     auto* k = k_pcg_resident<T, X, V, VAR, LX, LY>;
     const size_t lds = ResShape<LX, LY, V>::lds(sizeof(typename Traits<T>::C), VAR);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k, dim3((unsigned)a.plan.geo.G), dim3(RT), lds, s, a.plan.geo, static_cast<const T*>(a.r),
-                       static_cast<X*>(a.x), a.kc, static_cast<const T*>(a.dinv), a.st, a.hist, a.slots, a.surf, a.base,
-                       a.out, a.timing);
+    hipLaunchKernelGGL(k, dim3((unsigned)p.geo.G), dim3(RT), lds, s, a);
     return hipGetLastError();
 }
 
-template <typename T, typename X, bool VAR, int LX, int LY> hipError_t pick_v(const ResLaunch& a, hipStream_t s) {
+template <typename T, typename X, bool VAR, int LX, int LY> hipError_t pick_v(const ResPlan& p, const ResTask& a, hipStream_t s) {
     constexpr int most = res_most_v(sizeof(typename Traits<T>::C) == 8, VAR);
     hipError_t e = hipErrorInvalidValue;
     auto one = [&]<int V>() {
         if constexpr (V <= most)
-            if (a.plan.V == V) e = run_resident<T, X, V, VAR, LX, LY>(a, s);
+            if (p.V == V) e = run_resident<T, X, V, VAR, LX, LY>(p, a, s);
     };
     [&]<int... V>(std::integer_sequence<int, V...>) {
         (one.template operator()<V>(), ...);
@@ -605,11 +807,11 @@ template <typename T, typename X, bool VAR, int LX, int LY> hipError_t pick_v(co
     return e;
 }
 
-template <typename T, typename X, bool VAR> hipError_t pick_shape(const ResLaunch& a, hipStream_t s) {
-    const int lx = a.plan.geo.lx, ly = a.plan.geo.ly;
-    if (lx == 5 && ly == 4) return pick_v<T, X, VAR, 5, 4>(a, s);
-    if (lx == 4 && ly == 4) return pick_v<T, X, VAR, 4, 4>(a, s);
-    if (lx == 3 && ly == 4) return pick_v<T, X, VAR, 3, 4>(a, s);
+template <typename T, typename X, bool VAR> hipError_t pick_shape(const ResPlan& p, const ResTask& a, hipStream_t s) {
+    const int lx = p.geo.lx, ly = p.geo.ly;
+    if (lx == 5 && ly == 4) return pick_v<T, X, VAR, 5, 4>(p, a, s);
+    if (lx == 4 && ly == 4) return pick_v<T, X, VAR, 4, 4>(p, a, s);
+    if (lx == 3 && ly == 4) return pick_v<T, X, VAR, 3, 4>(p, a, s);
     return hipErrorInvalidValue;
 }
 

@@ -415,6 +415,7 @@ void plan_resident(pcg_ctx c) {
         if (c->res_mem) (void)hipFree(c->res_mem);
         c->res_bytes = 0;
         if (hipMalloc(&c->res_mem, need) != hipSuccess) {
+            (void)hipGetLastError();  // not the next launch's error
             c->res_mem = nullptr;
             return;
         }
@@ -424,41 +425,35 @@ void plan_resident(pcg_ctx c) {
     c->res_ok = true;
 }
 
-// Run a started solve to its end on the chip. *ran is false when its
-// work-groups could not be brought together: the vectors may then hold a mix
-// of the start and the end of the solve, and the caller starts over.
-pcg_status run_resident(pcg_ctx c, SolveState* fin, IterResult* out, bool* ran) {
+// Launch a task on the chip and wait for its result (c->hres_out; with
+// copy_state also c->hst[1]). *ran is false when its work-groups could not be
+// brought together: the task's outputs may then hold a mix of its start and
+// its end, and the caller starts over in another form.
+pcg_status run_resident(pcg_ctx c, ResTask& a, bool copy_state, bool* ran) {
     *ran = false;
     CuHold hold(c->dev, c->res_plan.geo.G, c->cus, 2.0);
     if (!hold.ok()) return PCG_OK;
     hipStream_t st = c->stream;
     char* const mem = static_cast<char*>(c->res_mem);
-    ResLaunch a{};
-    a.plan = c->res_plan;
-    a.r = c->r;
-    a.x = c->xacc;
+    a.geo = c->res_plan.geo;
     a.kc = c->kc;
     a.dinv = op_of(c).dinv;
-    a.st = c->st;
     a.hist = c->hist;
     a.slots = mem + RES_HEAD_BYTES;
     a.surf = mem + RES_HEAD_BYTES + RES_SLOT_BYTES;
     a.base = c->res_next;
     a.out = reinterpret_cast<ResOut*>(mem);
     a.timing = c->opt.kernel_timing;
-    HIPCHK(launch_pcg_resident(c->dt, c->opt.x_accum, a, st));
-    HIPCHK(hipMemcpyAsync(&c->hst[1], c->st, sizeof(SolveState), hipMemcpyDeviceToHost, st));
+    a.wait = RES_WAIT_TICKS;
+    HIPCHK(launch_pcg_resident(c->dt, c->opt.x_accum, c->res_plan, a, st));
+    if (copy_state) HIPCHK(hipMemcpyAsync(&c->hst[1], c->st, sizeof(SolveState), hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(c->hres_out, mem, sizeof(ResOut), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     if (c->hres_out->timeout) {
         c->res_timeout = true;
         return PCG_OK;
     }
-    *fin = c->hst[1];
-    c->res_next += (uint32_t)fin->iters + 2;
-    out->k1_ms = 1e-5 * (double)c->hres_out->ticks1;
-    out->k2_ms = 1e-5 * (double)c->hres_out->ticks2;
-    out->nk = fin->iters;
+    c->res_next += c->hres_out->used + 1;
     *ran = true;
     return PCG_OK;
 }
@@ -495,9 +490,17 @@ pcg_status run_iterations(pcg_ctx c, const void* b, const void* x0, int x0_dt, d
     const bool on_chip = allow_resident && c->res_ok && !c->res_timeout;
     if (on_chip) {
         bool ran = false;
-        s = run_resident(c, &out->fin, out, &ran);
+        ResTask a{};
+        a.r = c->r;
+        a.x = c->xacc;
+        a.st = c->st;
+        s = run_resident(c, a, true, &ran);
         if (s != PCG_OK) return s;
         if (!ran) return run_iterations(c, b, x0, x0_dt, rtol, maxit, stag, out, false);
+        out->fin = c->hst[1];
+        out->k1_ms = 1e-5 * (double)c->hres_out->ticks1;
+        out->k2_ms = 1e-5 * (double)c->hres_out->ticks2;
+        out->nk = out->fin.iters;
         c->last_iters = out->fin.iters;
         return PCG_OK;
     }
@@ -992,7 +995,37 @@ pcg_status pcg_solve(pcg_ctx c, const void* b, void* x, double rtol, int maxit, 
     int restarts = 0, total_iters = 0;
     const void* x0 = c->opt.use_x0 ? x : nullptr;
     int x0_dt = c->opt.x_dtype;
-    for (;;) {
+    bool solved = false;
+    if (c->res_ok && !c->res_timeout && !x0 && c->opt.x_dtype == DT_F64) {
+        // on the chip, start, FP64 judge and restarts included
+        Range r("PCG on the chip");
+        pcg_status s = ensure_hist(c, maxit);
+        if (s != PCG_OK) return s;
+        ResTask a{};
+        a.r = b;
+        a.r2 = c->r;
+        a.x = x;
+        a.rtol2 = rtol * rtol;
+        a.judge = 1;
+        a.maxit = maxit;
+        a.max_restarts = c->opt.max_restarts;
+        s = run_resident(c, a, false, &solved);
+        if (s != PCG_OK) return s;
+        if (solved) {
+            const ResOut& o = *c->hres_out;
+            total_iters = o.iters;
+            restarts = o.restarts;
+            c->last_iters = o.last_iters;
+            c->hres[0] = o.rr_true;
+            res.fin.done = o.done;
+            res.fin.rr = o.rr;
+            res.fin.rr0 = o.rr0;
+            res.k1_ms = 1e-5 * (double)o.ticks1;
+            res.k2_ms = 1e-5 * (double)o.ticks2;
+            res.nk = o.iters;
+        }
+    }
+    while (!solved) {
         IterResult seg;  // run_iterations accumulates its kernel times into a fresh result
         pcg_status s;
         {
