@@ -35,6 +35,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <new>
 #include <numeric>
 #include <string>
 #include <vector>
@@ -692,14 +693,11 @@ pcg_status upload_plans(BatchImpl& B) {
     return PCG_OK;
 }
 
-// How long a launch waits for other persistent launches of this process to
-// end (it fills the device, so it holds every CU); it starts anyway when that
-// runs out, and its own barrier bound then decides.
-constexpr double BATCH_HOLD_S = 10.0;
-
 // Run the whole batch eagerly and read back per-problem results.
 pcg_status run_once(BatchImpl& B, const float* b, double* x, double rtol2, int maxit, int* herr) {
-    CuHold hold(B.dev, B.cus, B.cus, BATCH_HOLD_S);
+    // The launch fills the device, so it claims every CU; without the claim it
+    // starts anyway and its own barrier bound decides.
+    CuHold hold(B.dev, B.cus, B.cus, RES_HOLD_S);
     BCHK(enqueue_batch(B, b, x, rtol2, maxit, B.stream));
     BCHK(hipMemcpyAsync(B.h_out, B.out, sizeof(BatchOut) * B.nprob, hipMemcpyDeviceToHost, B.stream));
     BCHK(hipMemcpyAsync(herr, B.err, sizeof(int), hipMemcpyDeviceToHost, B.stream));
@@ -795,7 +793,7 @@ bool res_schedule(const BatchImpl& B, int nwg, ResSchedule* out) {
 
 // Plan and workspace of the on-chip form; without either the streaming kernel
 // serves the batch.
-void res_prepare(BatchImpl& B) {
+void res_prepare(BatchImpl& B) try {
     B.res_ok = false;
     const int nwg = std::min(B.cus, RES_MAX_WG);
     ResSchedule sc;
@@ -866,6 +864,8 @@ void res_prepare(BatchImpl& B) {
         return;
     if (hipStreamSynchronize(B.stream) != hipSuccess) return;
     B.res_ok = true;
+} catch (const std::bad_alloc&) {
+    B.res_ok = false;
 }
 
 // The whole batch on the chip; results in B.h_out as the streaming kernel
@@ -1202,7 +1202,7 @@ pcg_status pcg_batch_solve(pcg_batch bt, const float* b, double* x, double rtol,
     BatchImpl& B = bt->impl;
     const auto t0 = std::chrono::steady_clock::now();
     const double rtol2 = rtol * rtol;
-    CuHold hold(B.dev, B.cus, B.cus, BATCH_HOLD_S);
+    CuHold hold(B.dev, B.cus, B.cus, RES_HOLD_S);
     bool on_chip = false;
     if (B.res_ok && hold.ok()) {
         const pcg_status st = res_solve(B, b, x, rtol2, maxit, &on_chip);

@@ -75,11 +75,18 @@ hipError_t launch_pcg_resident(int dt, int xdt, const ResPlan& p, const ResTask&
 
 namespace {
 
-// CUs of each device that persistent launches of this process hold.
+constexpr int MAX_DEVICES = 16;
+
+// CUs of each device that persistent launches of this process hold, and the
+// claims that wait for some, in the order they came. The queue is served from
+// its head only: a batch, which needs every CU, is not passed by solves that
+// need a few. A waiting claim is a node of the list itself (no allocation).
 struct Held {
     std::mutex m;
     std::condition_variable cv;
-    int used[16] = {};
+    int used[MAX_DEVICES] = {};
+    CuHold* head[MAX_DEVICES] = {};
+    CuHold* tail[MAX_DEVICES] = {};
 };
 Held& held() {
     static Held h;
@@ -89,11 +96,20 @@ Held& held() {
 }  // namespace
 
 CuHold::CuHold(int dev, int want, int cap, double wait_s) : dev_(dev), want_(want) {
-    if (dev < 0 || dev >= 16 || want > cap) return;
+    if (dev < 0 || dev >= MAX_DEVICES || want > cap) return;
     Held& h = held();
-    std::unique_lock<std::mutex> l(h.m);
-    ok_ = h.cv.wait_for(l, std::chrono::duration<double>(wait_s), [&] { return h.used[dev] + want <= cap; });
-    if (ok_) h.used[dev] += want;
+    {
+        std::unique_lock<std::mutex> l(h.m);
+        (h.tail[dev] ? h.tail[dev]->next_ : h.head[dev]) = this;
+        prev_ = h.tail[dev];
+        h.tail[dev] = this;
+        ok_ = h.cv.wait_for(l, std::chrono::duration<double>(wait_s),
+                            [&] { return h.head[dev] == this && h.used[dev] + want <= cap; });
+        (prev_ ? prev_->next_ : h.head[dev]) = next_;
+        (next_ ? next_->prev_ : h.tail[dev]) = prev_;
+        if (ok_) h.used[dev] += want;
+    }
+    h.cv.notify_all();  // the next in the queue may fit as well
 }
 
 CuHold::~CuHold() {

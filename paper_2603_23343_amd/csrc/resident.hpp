@@ -100,6 +100,9 @@ struct ResTask {
     long long wait;  // ticks (10 ns) a work-group waits in a grid sum at most
 };
 constexpr long long RES_WAIT_TICKS = 100000000;  // 1 s
+// How long a launch waits for its CUs on the host at most (results would
+// otherwise depend on what else runs: the other forms sum in another order).
+constexpr double RES_HOLD_S = 30.0;
 
 // One problem of a batch: its task and its compiled shape.
 struct ResBatchTask {
@@ -125,8 +128,9 @@ hipError_t launch_resident_f64(const ResPlan& p, const ResTask& a, hipStream_t s
 
 // A claim on CUs of a device for the time of a persistent launch: its
 // work-groups wait for each other, so two such launches of this process may
-// only overlap while both fit. Waits up to wait_s for others to end; ok() is
-// false if it ran out (the caller then takes a form that needs no claim).
+// only overlap while both fit. Claims are served in the order they come. Waits
+// up to wait_s for others to end; ok() is false if it ran out (the caller then
+// takes a form that needs no claim).
 class CuHold {
 public:
     CuHold(int dev, int want, int cap, double wait_s);
@@ -138,6 +142,7 @@ public:
 private:
     int dev_, want_;
     bool ok_ = false;
+    CuHold *prev_ = nullptr, *next_ = nullptr;  // in the queue of waiting claims
 };
 
 }  // namespace pcgmi

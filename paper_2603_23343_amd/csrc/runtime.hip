@@ -432,7 +432,7 @@ void plan_resident(pcg_ctx c) {
 // its end, and the caller starts over in another form.
 pcg_status run_resident(pcg_ctx c, ResTask& a, bool copy_state, bool* ran) {
     *ran = false;
-    CuHold hold(c->dev, c->res_plan.geo.G, c->cus, 2.0);
+    CuHold hold(c->dev, c->res_plan.geo.G, c->cus, RES_HOLD_S);
     if (!hold.ok()) return PCG_OK;
     hipStream_t st = c->stream;
     char* const mem = static_cast<char*>(c->res_mem);
