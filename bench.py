@@ -24,13 +24,13 @@ Also reported on the same JSON line:
                    each grid of --learned-n (64 and 128
                    by default);
   paper_grid    -- PCG time per iteration on the paper's 512 x 112 x 64
-                   comparison grid (FP32 with two kernels or the
-                   single-reduction form, and BF16 storage), beside the
+                   comparison grid (FP32 on the chip, with two kernels or in
+                   the single-reduction form, and BF16 storage), beside the
                    paper's own per-iteration times (context, other hardware);
-  small_grid    -- the 32^3 workload with both iteration forms;
+  small_grid    -- the 32^3 workload with the three iteration forms;
   slab          -- one GPU's share of the 256^3 system split in z over 8
-                   GPUs (256 x 256 x 32 planes): the iteration kernels on that
-                   shape, the stencil over the slab with its two halo planes,
+                   GPUs (256 x 256 x 32 planes): the two iteration kernels on
+                   that shape, the stencil over the slab with its two halo planes,
                    and the halo bytes an iteration would exchange;
   kernels_512   -- standalone stencil / axpy / dot at 512^3 (FP32 and BF16),
                    achieved GB/s of algorithmic bytes, beside torch's device
@@ -42,9 +42,9 @@ Also reported on the same JSON line:
                    the matrix-free solves; a ragged random SPD matrix (1 M rows)
                    with and without sigma sorting;
   batched       -- 64 uneven problems (edges log-uniform in [16, 128], seed 5;
-                   b_i ~ U[-1,1], seeds 1000 + i) in one persistent
-                   hipGraph-captured launch: solves/s, per-problem latency,
-                   against 64 sequential pcg_solve calls;
+                   b_i ~ U[-1,1], seeds 1000 + i) in one persistent launch (on
+                   the chip): solves/s, per-problem latency, against 64
+                   sequential pcg_solve calls;
   cpu_baseline  -- the FP64 CPU oracle's Jacobi-PCG on the same system,
                    timed on a bounded number of iterations and scaled.
 """
@@ -293,16 +293,19 @@ PAPER_GRID_MS_PER_ITER = {"H100 FP32 (four separate kernels)": 0.28, "Wormhole B
 
 def bench_paper_grid(P, torch, steps):
     """PCG time per iteration on the paper's 512 x 112 x 64 comparison grid
-    (b ~ U[-1, 1], to recursive 1e-6 for FP32 and 1e-3 for BF16). 3.67 M
-    points: an iteration's vectors (73 MB FP32) sit in the last-level cache,
-    so this measures latency and cache bandwidth rather than HBM."""
+    (b ~ U[-1, 1], to recursive 1e-6 for FP32 and 1e-3 for BF16): the default
+    form (the grid held on the chip), the two-kernel form and the
+    single-reduction form. 3.67 M points: an iteration's vectors (73 MB FP32)
+    sit in the last-level cache, so the latter two measure latency and cache
+    bandwidth rather than HBM."""
     import synthetic
 
     nx, ny, nz = synthetic.PAPER_GRID
     N = nx * ny * nz
     b32 = torch.from_numpy(synthetic.uniform_f32(synthetic.SEED_PAPER_GRID_B, N)).cuda()
     out = {"grid": [nx, ny, nz], "paper_ms_per_iteration": PAPER_GRID_MS_PER_ITER}
-    for name, dt, xacc, xdt, tol, sr in (("f32", torch.float32, torch.float64, torch.float64, 1e-6, 0),
+    for name, dt, xacc, xdt, tol, sr in (("f32_on_chip", torch.float32, torch.float64, torch.float64, 1e-6, -1),
+                                         ("f32", torch.float32, torch.float64, torch.float64, 1e-6, 0),
                                          ("f32_single_reduction", torch.float32, torch.float64, torch.float64, 1e-6, 1),
                                          ("bf16", torch.bfloat16, torch.float32, torch.float64, 1e-3, 0)):
         ctx = P.pcg_create(nx, ny, nz, dt, x_accum=xacc, x_dtype=xdt, single_reduction=sr)
@@ -335,7 +338,8 @@ def bench_slab(P, torch, n=256, parts=8, iters=100):
     N = n * n * nzs
     b = torch.from_numpy(synthetic.uniform_f32(synthetic.SEED_C1_B, N)).cuda()
     x = torch.empty(N, dtype=torch.float64, device="cuda")
-    ctx = P.pcg_create(n, n, nzs, torch.float32, x_dtype=torch.float64, kernel_timing=1, max_restarts=0)
+    ctx = P.pcg_create(n, n, nzs, torch.float32, x_dtype=torch.float64, kernel_timing=1, max_restarts=0,
+                       single_reduction=0)
     P.pcg_solve(ctx, b, x, 1e-30, 20, raise_on_error=False)
     info = P.pcg_solve(ctx, b, x, 1e-30, iters, raise_on_error=False)
     k1 = info["k1_ms"] * 1e3 / max(info["k1_launches"], 1)
@@ -415,14 +419,14 @@ def bench_multigrid(P, torch, b, n, steps, jacobi_s, nu=1, oracle_budget_s=0.0):
 
 def bench_small_grid(P, torch, steps, n=32):
     """The small workload (n^3, b ~ U[-1, 1] seed 1, FP32 to 1e-6): solve time
-    with two kernels per iteration and with the single-reduction form (the
-    default at this size). Latency-bound: a few microseconds of work per kernel."""
+    on the chip (the default), with two kernels per iteration and with the
+    single-reduction form. Latency-bound: a few microseconds of work per kernel."""
     import synthetic
 
     N = n ** 3
     b = torch.from_numpy(synthetic.uniform_f32(synthetic.SEED_C1_B, N)).cuda()
     out = {"grid": n}
-    for name, sr in (("two_kernel", 0), ("single_reduction", 1)):
+    for name, sr in (("on_chip", -1), ("two_kernel", 0), ("single_reduction", 1)):
         ctx = P.pcg_create(n, n, n, torch.float32, x_dtype=torch.float64, single_reduction=sr)
         x = torch.empty(N, dtype=torch.float64, device="cuda")
         P.pcg_solve(ctx, b, x, 1e-6, 500, raise_on_error=False)
@@ -519,8 +523,8 @@ def cpu_baseline_sell(b32_host, n, gpu_iters, reps=3):
 
 
 def bench_batched(P, torch, reps, oracle_budget_s=0.0):
-    """The 64-problem batch: graph replays timed with torch events on the
-    stream the batch was created on (the current stream)."""
+    """The 64-problem batch timed with torch events on the stream the batch
+    was created on (the current stream)."""
     import synthetic
 
     sizes = synthetic.batch_sizes()
@@ -543,7 +547,8 @@ def bench_batched(P, torch, reps, oracle_budget_s=0.0):
     torch.cuda.synchronize()
     ms = ev0.elapsed_time(ev1) / reps
     lat = sorted(r["latency_s"])
-    # the batched kernel also advances x every second update (12 or 32 B/pt)
+    # what the streaming form moves (it advances x every second update: 12 or
+    # 32 B/pt): a rate to compare with, not the on-chip form's own traffic
     traffic = sum((BYTES_DIRECTION + update_bytes(it)) * it * m ** 3 for m, it in zip(sizes, r["iters"]))
     # the same 64 problems one after another through pcg_solve
     ctxs = []
@@ -566,13 +571,15 @@ def bench_batched(P, torch, reps, oracle_budget_s=0.0):
            "latency_ms": {"min": round(lat[0] * 1e3, 3), "median": round(lat[len(lat) // 2] * 1e3, 3),
                           "max": round(lat[-1] * 1e3, 3)},
            "effective_GB/s": round(traffic / (ms * 1e-3) / 1e9, 1),
+           "effective_note": "priced at the streaming form's 34 B per point-iteration; on the chip only box surfaces "
+                             "move",
            "iters_total": int(sum(r["iters"])), "restarts_total": int(sum(r["restarts"])),
            "status": P.STATUS_NAMES[r["status"]],
            "max_true_relres": max(r["relres"]), "sequential_ms": round(seq * 1e3, 2),
            "speedup_vs_sequential": round(seq * 1e3 / ms, 3),
            "iters_equal_sequential": int(sum(1 for a, c in zip(r["iters"], seq_iters) if a == c)),
            "work_groups": bt.grid, "create_and_tune_s": round(t_create, 3),
-           # per problem: edge, iterations, work-groups, latency (ms), in finishing order
+           # per problem: edge, iterations, work-groups of the streaming form, latency (ms), in finishing order
            "per_problem": sorted(([m, int(it), int(bt.plans[i][2]), round(lt * 1e3, 2)]
                                   for i, (m, it, lt) in enumerate(zip(sizes, r["iters"], r["latency_s"]))),
                                  key=lambda e: e[3])}
