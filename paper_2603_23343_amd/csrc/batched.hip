@@ -885,7 +885,7 @@ pcg_status res_solve(BatchImpl& B, const float* b, double* x, double rtol2, int 
         a.rtol2 = rtol2;
         a.base = B.res_next;
         a.judge = 1;
-        a.maxit = maxit;
+        a.maxit = std::max(maxit, 1);  // the streaming form runs at least one iteration, too
         a.max_restarts = B.max_restarts;
         a.wait = wait;
         B.h_res_tasks[i] = t;
