@@ -84,7 +84,9 @@ typedef struct {
                           fits (F32 or F64 storage, FP64 x accumulator, no tile or zchunk
                           given; up to about 4 M points in F32, half of that in F64 or with
                           cell coefficients), else chosen by grid size. On the chip the
-                          iterates are those of 0 (other summation order), use_graph,
+                          iterates are those of 0 (other summation order; a right-hand
+                          side whose squares FP32 cannot hold is scaled by a power of two
+                          on the way), use_graph,
                           chunk_iters and x_defer change nothing, and solves of one process
                           take turns on a device once their work-groups would exceed its
                           CUs */

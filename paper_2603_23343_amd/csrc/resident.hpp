@@ -60,7 +60,7 @@ struct ResOut {
     int last_iters;  // iterations since the last restart
     int restarts;
     uint32_t used;   // numbers of grid sums used
-    double rr, rr0, rr_true;       // recursive ||r||^2, ||b||^2, FP64 ||b - A x||^2 (judge)
+    double rr, rr0, rr_true;       // recursive ||r||^2, ||b||^2, FP64 ||b - A x||^2 (judge), up to one common factor
     long long ticks1, ticks2;      // wall-clock ticks (10 ns) of the two phases
     long long t_begin, t_done;     // wall clock (judge)
 };

@@ -236,6 +236,21 @@ template <typename T, int POLICY = 0> __device__ __forceinline__ void set_at(Buf
         __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), b, off, 0, POLICY);
 }
 
+// A solve with ||r||^2 = rr over n points is scaled by 2^scale_of(rr, n): 0
+// while the mean square lies within 2^-60 .. 2^60, else what brings it to about
+// 1. The partial sums are FP32 squares, which underflow below 1e-19 and overflow
+// above 1e19; within the bounds they stay normal numbers to a relative residual
+// of 1e-9. Multiplying by a power of two commutes with every rounding, so a
+// scaled solve has the bits of an unscaled one wherever that is in range.
+__device__ __forceinline__ int scale_of(double rr, double n) {
+    const double ms = rr / n;
+    if (!(ms > 0.0) || !isfinite(ms)) return 0;
+    const int e = __builtin_amdgcn_readfirstlane(ilogb(ms));
+    return abs(e) <= 60 ? 0 : -(e / 2);
+}
+__device__ __forceinline__ float times_2(float v, int e) { return __builtin_amdgcn_ldexpf(v, e); }
+__device__ __forceinline__ double times_2(double v, int e) { return __builtin_amdgcn_ldexp(v, e); }
+
 // Face coefficients of a thread's points (variable operator), computed once.
 template <typename C, int V, bool VAR> struct Faces {
     C l[V], r[V], d[V], u[V], z[V + 1];
@@ -269,16 +284,18 @@ __device__ __forceinline__ bool solve_box(const ResTask& a, const int rank, unsi
     // by other kernels, else (judge) formed here from b.
     double rr0 = 0.0, tol2 = 0.0, dconst = 1.0 / 6.0, rho = 0.0, beta_d = 0.0, rr = 0.0, stag_best = 0.0;
     int maxit = a.maxit, stag = 0, iters = 0, done = 0, stag_at = 0;
+    int scale = 0;  // r, p, q and x are 2^scale times the system's; rr, rho, sigma and tol2 4^scale times
     if (!judge) {
         if (st->done != 0 || st->maxit <= 0) return true;  // the same in every work-group
-        rr0 = uniform(st->rr0);
-        tol2 = uniform(st->tol2);
+        scale = scale_of(st->rr, (double)g.nx * g.ny * g.nz);
+        rr0 = uniform(times_2(st->rr0, 2 * scale));
+        tol2 = uniform(times_2(st->tol2, 2 * scale));
         dconst = uniform(st->dinv);
         maxit = st->maxit;
         stag = st->stag;
-        rho = uniform(st->rho);
+        rho = uniform(times_2(st->rho, 2 * scale));
         beta_d = uniform(st->beta);
-        rr = uniform(st->rr);
+        rr = uniform(times_2(st->rr, 2 * scale));
         stag_best = uniform(st->stag_best);
         iters = st->iters;
         stag_at = st->stag_at;
@@ -404,7 +421,7 @@ __device__ __forceinline__ bool solve_box(const ResTask& a, const int rank, unsi
 #pragma unroll
     for (int v = 0; v < V; ++v) {
         p[v] = q[v] = r[v] = C(0);
-        const double xv = (double)to_c(get_at<X>(xbuf, gp + v * gz, v < nv && !judge));
+        const double xv = times_2((double)to_c(get_at<X>(xbuf, gp + v * gz, v < nv && !judge)), scale);
         if constexpr (VAR) {
             xlds[v * RT + t] = xv;
             dv[v] = to_c(get_at<T>(dbuf, gp + v * gz, v < nv));
@@ -488,9 +505,10 @@ __device__ __forceinline__ bool solve_box(const ResTask& a, const int rank, unsi
             double tot[NB];
             late = !sum_collect<NB>(tot, L, slots, 1, rank, G, no, a.wait);
             ++no;
-            rr0 = rr = tot[0];
+            scale = scale_of(tot[0], (double)npts);
+            rr0 = rr = uniform(times_2(tot[0], 2 * scale));
             tol2 = uniform(a.rtol2 * rr0);
-            rho = VAR ? tot[NB - 1] : uniform(dconst * rr0);
+            rho = VAR ? uniform(times_2(tot[NB - 1], 2 * scale)) : uniform(dconst * rr0);
             rr_true = rr0;
             if (!isfinite(rr0)) done = 2;
             else if (rr0 == 0.0 || rr <= tol2) done = 1;
@@ -498,6 +516,14 @@ __device__ __forceinline__ bool solve_box(const ResTask& a, const int rank, unsi
             if (keeper && hist) hist[0] = rr;
         }
         if (late) break;
+        if (scale != 0 && restarts == 0) {  // a restart's residual is stored scaled
+#pragma unroll
+            for (int v = 0; v < V; ++v) r[v] = times_2(r[v], scale);
+#pragma unroll
+            for (int m = 0; m < HG; ++m)
+#pragma unroll
+                for (int e = 0; e < GN; ++e) rh[m][e] = times_2(rh[m][e], scale);
+        }
         while (!done) {
             // ---- direction, q = A p, p.q. The neighbours' last q (zero before
             // the first update) brings the halo's residual up to date.
@@ -710,7 +736,7 @@ __device__ __forceinline__ bool solve_box(const ResTask& a, const int rank, unsi
                 } else {
                     ax = StencilConst<double>::apply(xc, xl, xr, xd, xu, xb, xa);
                 }
-                const double res = (double)to_c(get_at<T>(bbuf, gi, true)) - ax;
+                const double res = times_2((double)to_c(get_at<T>(bbuf, gi, true)), scale) - ax;
                 const T rs = from_c<T>((C)res);
                 const double rv = (double)to_c(rs);
                 set_at<T, AGENT>(r2buf, gi, true, rs);
@@ -744,7 +770,7 @@ __device__ __forceinline__ bool solve_box(const ResTask& a, const int rank, unsi
         if (t == 0) __hip_atomic_store(&a.out->timeout, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return false;
     }
-    if (!judge) {
+    if (!judge || scale != 0) {  // a judged x is in place, but for its scale
         const Own o = own();
         int ge = o.gi;
 #pragma unroll
@@ -752,7 +778,7 @@ __device__ __forceinline__ bool solve_box(const ResTask& a, const int rank, unsi
             double xv;
             if constexpr (VAR) xv = xlds[v * RT + t];
             else xv = x[v];
-            set_at<X>(xbuf, ge, v < o.nv, from_c<X>((typename Traits<X>::C)xv));
+            set_at<X>(xbuf, ge, v < o.nv, from_c<X>((typename Traits<X>::C)times_2(xv, -scale)));
             ge += gz;
             if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
@@ -763,11 +789,11 @@ __device__ __forceinline__ bool solve_box(const ResTask& a, const int rank, unsi
             for (int i = (judge ? 0 : first + 1) + t; i <= iters; i += RT) hist[i] = rr0 > 0.0 ? sqrt(hist[i] / rr0) : 0.0;
         if (t == 0) {
             if (!judge) {
-                st->rho = rho;
+                st->rho = times_2(rho, -2 * scale);
                 st->alpha = alpha_d64;
                 st->beta = beta_d;
-                st->sigma = sigma;
-                st->rr = rr;
+                st->sigma = times_2(sigma, -2 * scale);
+                st->rr = times_2(rr, -2 * scale);
                 st->iters = iters;
                 st->done = done;
                 st->stag_at = stag_at;

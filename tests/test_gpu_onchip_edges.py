@@ -1,0 +1,90 @@
+"""Right-hand sides and limits at the edges of the on-chip form: what a solve
+or a batch returns there must not depend on the form that runs it."""
+import numpy as np
+import pytest
+import torch
+
+import synthetic
+from gpu_helpers import dev, host64, make_vec
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    import paper_2603_23343_amd as P
+
+    return P
+
+
+def _times_2(t, e):
+    """t 2^e, exactly (torch.ldexp multiplies by a rounded power)."""
+    return dev(np.ldexp(t.cpu().numpy(), e))
+
+
+def _coef(seed, n):
+    return dev(np.exp(synthetic.uniform(seed, n)).astype(np.float32))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("coef", [False, True])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (3, 4, 5), (50, 60, 64)])
+def test_scaled_right_hand_side(P, dtype, coef, shape):
+    """b 2^e for powers of two far outside the range whose squares FP32 holds:
+    the solve takes the same steps as for b, so x is x(b) 2^e bit for bit."""
+    nz, ny, nx = shape
+    n = nx * ny * nz
+    b, _ = make_vec(71, n, dtype)
+    ctx = P.pcg_create(nx, ny, nz, dtype, x_dtype=torch.float64)
+    if coef:
+        k = _coef(72, n)
+        P.pcg_set_coefficients(ctx, k)
+    outs = []
+    for e in (0, -61, -75, -90, 63, 90):
+        x = torch.full((n,), np.nan, dtype=torch.float64, device="cuda")
+        info = P.pcg_solve(ctx, _times_2(b, e), x, 1e-5, 1000, raise_on_error=False)
+        print(shape, dtype, coef, e, info["status"], info["iters"], info["rel_res_true_fp64"], flush=True)
+        outs.append((info["status"], info["iters"], info["restarts"], np.ldexp(host64(x), -e)))
+    assert outs[0][0] == P.PCG_OK
+    for o in outs[1:]:
+        assert o[:3] == outs[0][:3]
+        assert np.array_equal(o[3], outs[0][3])
+
+
+@pytest.mark.parametrize("coef", [False, True])
+@pytest.mark.parametrize("e", [-61, -75, -90])
+def test_scaled_right_hand_side_started_outside(P, coef, e):
+    """With an FP32 x other kernels make the start and judge the result; their
+    start sums squares in FP32 and may take a small b for zero (the judge then
+    restarts), so only the outcome is compared: the FP64 judge accepts x."""
+    nx, ny, nz = 20, 12, 9
+    n = nx * ny * nz
+    b, _ = make_vec(74, n, torch.float32)
+    ctx = P.pcg_create(nx, ny, nz, torch.float32)
+    if coef:
+        k = _coef(75, n)
+        P.pcg_set_coefficients(ctx, k)
+    x = torch.full((n,), np.nan, dtype=torch.float32, device="cuda")
+    info = P.pcg_solve(ctx, _times_2(b, e), x, 1e-5, 1000, raise_on_error=False)
+    print(info, flush=True)
+    assert info["status"] == P.PCG_OK and info["rel_res_true_fp64"] <= 1e-5
+
+
+def test_scaled_right_hand_side_batch(P):
+    """As above in a batch, each problem with another power of two."""
+    dims = [(1, 1, 1), (5, 4, 3), (17, 17, 17), (33, 20, 40), (24, 24, 24)]
+    bt = P.pcg_batch_create(dims)
+    b = dev(synthetic.uniform_f32(73, bt.total))
+    x = torch.full((bt.total,), np.nan, dtype=torch.float64, device="cuda")
+    r0 = P.pcg_batch_solve(bt, b, x, 1e-6, 1000)
+    want = [host64(bt.view(x, i)) for i in range(len(dims))]
+    exps = [-90, -75, 90, -61, 63]
+    for i, e in enumerate(exps):
+        v = bt.view(b, i)
+        v.copy_(_times_2(v, e))
+    r = P.pcg_batch_solve(bt, b, x, 1e-6, 1000, raise_on_error=False)
+    print(r, flush=True)
+    assert r["status"] == P.PCG_OK
+    assert r["iters"] == r0["iters"] and r["restarts"] == r0["restarts"]
+    for i, e in enumerate(exps):
+        assert np.array_equal(np.ldexp(host64(bt.view(x, i)), -e), want[i])
