@@ -887,6 +887,7 @@ pcg_status res_solve(BatchImpl& B, const float* b, double* x, double rtol2, int 
         a.judge = 1;
         a.maxit = std::max(maxit, 1);  // the streaming form runs at least one iteration, too
         a.max_restarts = B.max_restarts;
+        a.step_first = 1;
         a.wait = wait;
         B.h_res_tasks[i] = t;
     }

@@ -97,6 +97,7 @@ struct ResTask {
     uint32_t base;  // number of the first grid sum (never used before on these slots)
     int timing;
     int judge, maxit, max_restarts;
+    int step_first;  // judge: a start within the tolerance is iterated all the same (as the streaming batch does)
     long long wait;  // ticks (10 ns) a work-group waits in a grid sum at most
 };
 constexpr long long RES_WAIT_TICKS = 100000000;  // 1 s

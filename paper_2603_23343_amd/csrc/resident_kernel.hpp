@@ -511,7 +511,7 @@ __device__ __forceinline__ bool solve_box(const ResTask& a, const int rank, unsi
             rho = VAR ? uniform(times_2(tot[NB - 1], 2 * scale)) : uniform(dconst * rr0);
             rr_true = rr0;
             if (!isfinite(rr0)) done = 2;
-            else if (rr0 == 0.0 || rr <= tol2) done = 1;
+            else if (rr0 == 0.0 || (rr <= tol2 && !a.step_first)) done = 1;
             else if (maxit <= 0) done = 3;
             if (keeper && hist) hist[0] = rr;
         }
@@ -763,7 +763,7 @@ __device__ __forceinline__ bool solve_box(const ResTask& a, const int rank, unsi
         beta_d = 0.0;
         iters = seg0 = 0;
         maxit = a.maxit - total;
-        done = !isfinite(rr) ? 2 : rr <= tol2 ? 1 : 0;
+        done = !isfinite(rr) ? 2 : rr == 0.0 || (rr <= tol2 && !a.step_first) ? 1 : 0;
         if (keeper && hist) hist[0] = rr;
     }
     if (late) {

@@ -88,3 +88,22 @@ def test_scaled_right_hand_side_batch(P):
     assert r["iters"] == r0["iters"] and r["restarts"] == r0["restarts"]
     for i, e in enumerate(exps):
         assert np.array_equal(np.ldexp(host64(bt.view(x, i)), -e), want[i])
+
+
+@pytest.mark.parametrize("rtol", [1.0, 2.0])
+@pytest.mark.parametrize("maxit", [0, 1, 50])
+def test_batch_takes_one_step_at_least(P, orc, rtol, maxit):
+    """A batch iterates before it judges: with a tolerance that x = 0 meets
+    every problem ends after one step (the streaming form's answer). One CG step
+    in FP32: the norms and the update are good to a few 2^-24 per term."""
+    dims = [(5, 4, 3), (17, 17, 17), (33, 20, 40)]
+    bt = P.pcg_batch_create(dims)
+    b = dev(synthetic.uniform_f32(76, bt.total))
+    x = torch.full((bt.total,), np.nan, dtype=torch.float64, device="cuda")
+    r = P.pcg_batch_solve(bt, b, x, rtol, maxit)
+    print(r, flush=True)
+    assert r["iters"] == [1, 1, 1] and r["restarts"] == [0, 0, 0]
+    for i, (nx, ny, nz) in enumerate(dims):
+        ref = orc.pcg((nz, ny, nx), host64(bt.view(b, i)), rtol=0.0, maxit=1)
+        xi = host64(bt.view(x, i))
+        assert np.linalg.norm(xi - ref["x"]) <= 32 * 2.0 ** -24 * np.linalg.norm(ref["x"])
