@@ -1205,7 +1205,12 @@ pcg_status pcg_batch_solve(pcg_batch bt, const float* b, double* x, double rtol,
     const double rtol2 = rtol * rtol;
     CuHold hold(B.dev, B.cus, B.cus, RES_HOLD_S);
     bool on_chip = false;
-    if (B.res_ok && hold.ok()) {
+    // On the chip x is written before its residual is formed from b. The
+    // streaming form copies b at its start and writes x last, so a batch of one
+    // problem may be solved in place there.
+    const uintptr_t b0 = reinterpret_cast<uintptr_t>(b), x0 = reinterpret_cast<uintptr_t>(x);
+    const bool apart = b0 + (size_t)B.total * sizeof(float) <= x0 || x0 + (size_t)B.total * sizeof(double) <= b0;
+    if (B.res_ok && hold.ok() && apart) {
         const pcg_status st = res_solve(B, b, x, rtol2, maxit, &on_chip);
         if (st != PCG_OK) return st;
     }
