@@ -286,7 +286,13 @@ __device__ __forceinline__ bool solve_box(const ResTask& a, const int rank, unsi
     int maxit = a.maxit, stag = 0, iters = 0, done = 0, stag_at = 0;
     int scale = 0;  // r, p, q and x are 2^scale times the system's; rr, rho, sigma and tol2 4^scale times
     if (!judge) {
-        if (st->done != 0 || st->maxit <= 0) return true;  // the same in every work-group
+        if (st->done != 0 || st->maxit <= 0) {  // the same in every work-group
+            if (rank == 0 && threadIdx.x == 0) {
+                a.out->used = 0;
+                a.out->ticks1 = a.out->ticks2 = 0;
+            }
+            return true;
+        }
         scale = scale_of(st->rr, (double)g.nx * g.ny * g.nz);
         rr0 = uniform(times_2(st->rr0, 2 * scale));
         tol2 = uniform(times_2(st->tol2, 2 * scale));

@@ -125,3 +125,20 @@ def test_batch_in_place(P):
     assert abs(r["iters"][0] - r0["iters"][0]) <= 1
     # || x - y || <= 2 cond(A) rtol ||x||, cond(A) below 500 on this grid
     assert torch.linalg.norm(x - y) <= 1e-3 * torch.linalg.norm(x)
+
+
+def test_times_of_a_solve_without_iterations(P):
+    """A start that other kernels judged as finished reports no iteration time,
+    whatever the context solved before."""
+    n = 20 * 20 * 20
+    b, _ = make_vec(78, n, torch.float32)
+    ctx = P.pcg_create(20, 20, 20, torch.float32, kernel_timing=1)  # FP32 x: started outside
+    x = torch.empty(n, device="cuda")
+    info = P.pcg_solve(ctx, b, x, 1e-4, 500)
+    assert info["k1_launches"] == info["iters"] > 0 and info["k1_ms"] > 0 and info["k2_ms"] > 0
+    info = P.pcg_solve(ctx, torch.zeros_like(b), x, 1e-4, 500)
+    print(info, flush=True)
+    assert info["iters"] == info["k1_launches"] == 0
+    assert info["k1_ms"] == 0 and info["k2_ms"] == 0
+    info = P.pcg_solve(ctx, b, x, 1e-4, 500)
+    assert info["k1_launches"] == info["iters"] > 0 and info["k1_ms"] > 0 and info["k2_ms"] > 0
