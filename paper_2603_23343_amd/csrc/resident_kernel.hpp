@@ -475,7 +475,7 @@ __device__ __forceinline__ bool solve_box(const ResTask& a, const int rank, unsi
     int restarts = 0, total = 0;
     double rr_true = 0.0;
     const bool keeper = rank == 0 && t == 0;
-    long long t1 = 0, t2 = 0, mark = a.timing ? wall_clock64() : 0;
+    long long t1 = 0, t2 = 0, mark = 0;
     for (;;) {  // segments: the solve, then its restarts
         {
             const Buf rbuf = restarts ? r2buf : bbuf;
@@ -530,6 +530,7 @@ __device__ __forceinline__ bool solve_box(const ResTask& a, const int rank, unsi
 #pragma unroll
                 for (int e = 0; e < GN; ++e) rh[m][e] = times_2(rh[m][e], scale);
         }
+        if (a.timing) mark = wall_clock64();  // the phases only: no load, norm or judge of a segment
         while (!done) {
             // ---- direction, q = A p, p.q. The neighbours' last q (zero before
             // the first update) brings the halo's residual up to date.

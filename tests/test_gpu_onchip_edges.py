@@ -142,3 +142,20 @@ def test_times_of_a_solve_without_iterations(P):
     assert info["k1_ms"] == 0 and info["k2_ms"] == 0
     info = P.pcg_solve(ctx, b, x, 1e-4, 500)
     assert info["k1_launches"] == info["iters"] > 0 and info["k1_ms"] > 0 and info["k2_ms"] > 0
+
+
+def test_phase_times_leave_out_the_start(P):
+    """k1_ms and k2_ms are an iteration's two phases: a solve of one iteration,
+    which reads no surfaces, reports no more than one of a hundred takes (with a
+    quarter for noise, the least of ten solves): no loads, no norm before it."""
+    nx, ny, nz = 128, 128, 64
+    n = nx * ny * nz
+    b, _ = make_vec(79, n, torch.float32)
+    ctx = P.pcg_create(nx, ny, nz, torch.float32, x_dtype=torch.float64, kernel_timing=1, max_restarts=0)
+    x = torch.empty(n, dtype=torch.float64, device="cuda")
+    many = [P.pcg_solve(ctx, b, x, 1e-30, 100, raise_on_error=False) for _ in range(3)]
+    one = [P.pcg_solve(ctx, b, x, 1e-30, 1, raise_on_error=False) for _ in range(10)]
+    each = min(i["k1_ms"] for i in many) / 100
+    print("phase 1 of 100:", each, "of 1:", [i["k1_ms"] for i in one], flush=True)
+    assert all(i["k1_launches"] == 1 for i in one)
+    assert min(i["k1_ms"] for i in one) <= 1.25 * each
