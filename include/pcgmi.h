@@ -122,7 +122,7 @@ typedef struct {
     int k1_launches, k2_launches;
     int restarts;            /* pcg_solve: FP64 residual restarts taken (max_restarts) */
     double k2_even_ms;       /* kernel_timing: the part of k2_ms spent in the updates of even
-                                iterations (those that advance x; x_defer = 1) */
+                                iterations (those that advance x; x_defer = 1; 0 on the chip) */
     int k2_even_launches;
 } pcg_info;
 
@@ -290,6 +290,18 @@ pcg_status pcg_solve_mg(pcg_ctx ctx, const void *b, void *x, double rtol, int ma
  * *count receives the number written. */
 pcg_status pcg_get_history(pcg_ctx ctx, double *hist, int n, int *count);
 
+/* Form of the iterations that the last pcg_solve, inner solve of
+ * pcg_solve_refined or Jacobi-PCG continuation on this context ran (the last
+ * one, where a solve went on in another form): PCG_FORM_NONE before any. The
+ * forms sum in different orders, so their results differ in the last bits. */
+typedef enum {
+    PCG_FORM_NONE = -1,
+    PCG_FORM_STREAMING = 0,        /* two kernels per iteration; a batch: its streaming kernel */
+    PCG_FORM_SINGLE_REDUCTION = 1, /* one kernel per iteration */
+    PCG_FORM_ON_CHIP = 2
+} pcg_form;
+pcg_status pcg_get_form(pcg_ctx ctx, int *form);
+
 /* ------------------------------------------------------------------------
  * Learned preconditioner (not in the paper): a 3D CNN z = rms(r) N(r / rms(r), g)
  * with four 3x3x3 convolution layers 2 -> 16 -> 16 -> 16 -> 1, zero
@@ -450,6 +462,10 @@ pcg_status pcg_batch_destroy(pcg_batch batch);
  * chip, and those whose group barriers ran in the XCD-local form (all of them
  * when every work-group ran on the XCD the layout assigns it)}. */
 pcg_status pcg_batch_layout(pcg_batch batch, int64_t *offsets, int64_t *total, int *plans, int *grid);
+
+/* Form of the last pcg_batch_solve: PCG_FORM_NONE before any,
+ * PCG_FORM_STREAMING or PCG_FORM_ON_CHIP. */
+pcg_status pcg_batch_get_form(pcg_batch batch, int *form);
 
 /* Group-barrier form of later solves: 0 (default) = XCD-local where a group's
  * work-groups all run on one XCD, agent-scope fences otherwise; 1 = agent-scope

@@ -23,6 +23,8 @@ LIBPATH = os.path.join(_HERE, "libpcgmi.so")
 SOLVE_OUTCOMES = (PCG_E_NOCONV, PCG_E_BREAKDOWN, PCG_E_TRUE_RESIDUAL)
 PCG_F32, PCG_BF16, PCG_F16, PCG_F64 = range(4)
 
+PCG_FORM_NONE, PCG_FORM_STREAMING, PCG_FORM_SINGLE_REDUCTION, PCG_FORM_ON_CHIP = range(-1, 3)
+
 STATUS_NAMES = {0: "PCG_OK", 1: "PCG_E_ARG", 2: "PCG_E_HIP", 3: "PCG_E_NOCONV", 4: "PCG_E_BREAKDOWN",
                 5: "PCG_E_NOMEM", 6: "PCG_E_UNSUPPORTED", 7: "PCG_E_TRUE_RESIDUAL"}
 
@@ -71,6 +73,8 @@ def _load():
         "dot_f64": ([vp, i64, vp, vp, vp], i),
         "dot_noalloc": ([i, i64, vp, vp, vp, vp, vp], i),
         "pcg_solve": ([vp, vp, vp, d, i, ctypes.POINTER(PcgInfo)], i),
+        "pcg_get_form": ([vp, ctypes.POINTER(i)], i),
+        "pcg_batch_get_form": ([vp, ctypes.POINTER(i)], i),
         "pcg_get_history": ([vp, ctypes.POINTER(d), i, ctypes.POINTER(i)], i),
         "pcg_solve_refined": ([vp, vp, vp, d, d, i, i, ctypes.POINTER(PcgInfo)], i),
         "pcg_refine_history": ([vp, ctypes.POINTER(d), ctypes.POINTER(i), i, ctypes.POINTER(i)], i),
@@ -278,6 +282,13 @@ def pcg_get_history(ctx: Context, n=1 << 20):
     _check(lib.pcg_get_history(ctx.handle, buf.ctypes.data_as(ctypes.POINTER(ctypes.c_double)), n,
                                ctypes.byref(cnt)))
     return buf[: cnt.value].copy()
+
+
+def pcg_get_form(ctx: Context) -> int:
+    """Form of the context's last Jacobi-PCG iterations (PCG_FORM_*)."""
+    f = ctypes.c_int()
+    _check(lib.pcg_get_form(ctx.handle, ctypes.byref(f)))
+    return f.value
 
 
 # Default inner tolerance of refinement per storage type, from a sweep at
@@ -552,6 +563,13 @@ def pcg_batch_create(dims, cfgs=None, cache_path=None, tune_iters=20, stream=Non
 
 def pcg_batch_destroy(batch: Batch):
     batch.close()
+
+
+def pcg_batch_get_form(batch: Batch) -> int:
+    """Form of the batch's last solve (PCG_FORM_*)."""
+    f = ctypes.c_int()
+    _check(lib.pcg_batch_get_form(batch.handle, ctypes.byref(f)))
+    return f.value
 
 
 def pcg_batch_set_restarts(batch: Batch, max_restarts: int):

@@ -445,6 +445,7 @@ struct BatchImpl {
     int xcd_local = 0;  // problems whose barriers ran XCD-local in the last solve
     int force_agent = 0;  // 1: every group barrier takes the agent-scope fence form
     int max_restarts = BATCH_MAX_RESTARTS;  // FP64-residual restarts per problem
+    int form = PCG_FORM_NONE;  // of the last solve
     int dev = 0, cus = 0;
     // on-chip form (resident_batch.hip)
     bool res_ok = false;
@@ -1166,6 +1167,12 @@ pcg_status pcg_batch_layout(pcg_batch bt, int64_t* offsets, int64_t* total, int*
     return PCG_OK;
 }
 
+pcg_status pcg_batch_get_form(pcg_batch bt, int* form) {
+    if (!bt || !form) return berr(PCG_E_ARG, "pcg_batch_get_form: null argument");
+    *form = bt->impl.form;
+    return PCG_OK;
+}
+
 static int status_rank(pcg_status s) {
     return s == PCG_E_BREAKDOWN ? 3 : s == PCG_E_NOCONV ? 2 : s == PCG_E_TRUE_RESIDUAL ? 1 : 0;
 }
@@ -1255,6 +1262,7 @@ pcg_status pcg_batch_solve(pcg_batch bt, const float* b, double* x, double rtol,
     }
     const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     if (seconds) *seconds = secs;
+    B.form = on_chip ? PCG_FORM_ON_CHIP : PCG_FORM_STREAMING;
     if (herr) return berr(PCG_E_HIP, "pcg_batch_solve: a group barrier timed out (work-groups not co-resident)");
     unsigned long long tmin = ~0ull;
     B.xcd_local = 0;

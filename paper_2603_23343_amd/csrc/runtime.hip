@@ -122,6 +122,7 @@ struct pcg_ctx_s {
     bool sr_active = false;
     hipEvent_t ev_chunk[2] = {nullptr, nullptr};
     int last_iters = 0;
+    int form = PCG_FORM_NONE;  // of the last Jacobi-PCG iterations
     // on-chip form (resident_kernel.hpp): plan for the current operator,
     // exchange buffers (zeroed once; sums are numbered, never reused)
     int dev = 0, cus = 0;
@@ -503,9 +504,11 @@ pcg_status run_iterations(pcg_ctx c, const void* b, const void* x0, int x0_dt, d
         out->k2_ms = 1e-5 * (double)c->hres_out->ticks2;
         out->nk = out->fin.iters;
         c->last_iters = out->fin.iters;
+        c->form = PCG_FORM_ON_CHIP;
         return PCG_OK;
     }
     c->sr_active = want_single_reduction(c);
+    c->form = c->sr_active ? PCG_FORM_SINGLE_REDUCTION : PCG_FORM_STREAMING;
     if (c->sr_active) {
         // w0 = A D^-1 r0 and {gamma0, delta0}; s_{-1} = 0 (p_{-1} = 0 from the start above)
         const size_t vb = (size_t)c->n * dt_size(c->dt);
@@ -1017,6 +1020,7 @@ pcg_status pcg_solve(pcg_ctx c, const void* b, void* x, double rtol, int maxit, 
             total_iters = o.iters;
             restarts = o.restarts;
             c->last_iters = o.last_iters;
+            c->form = PCG_FORM_ON_CHIP;
             c->hres[0] = o.rr_true;
             res.fin.done = o.done;
             res.fin.rr = o.rr;
@@ -1586,6 +1590,12 @@ pcg_status pcg_mg_levels(pcg_ctx c, int* nlev, int* dims) {
             dims[3 * l + 1] = c->mg->lv[l].ny;
             dims[3 * l + 2] = c->mg->lv[l].nz;
         }
+    return PCG_OK;
+}
+
+pcg_status pcg_get_form(pcg_ctx c, int* form) {
+    if (!c || !form) return fail(PCG_E_ARG, "pcg_get_form: null argument");
+    *form = c->form;
     return PCG_OK;
 }
 
