@@ -5,6 +5,8 @@
 
 #include "internal.hpp"
 
+struct pcg_ctx_s;
+
 namespace pcgmi {
 
 constexpr int RES_MAX_WG = 256;                    // one work-group per CU
@@ -126,6 +128,11 @@ hipError_t launch_pcg_resident(int dt, int xdt, const ResPlan& p, const ResTask&
 hipError_t launch_resident_f32(const ResPlan& p, const ResTask& a, hipStream_t s);
 hipError_t launch_resident_f32_var(const ResPlan& p, const ResTask& a, hipStream_t s);
 hipError_t launch_resident_f64(const ResPlan& p, const ResTask& a, hipStream_t s);
+
+// For tests of what follows a launch whose work-groups did not come together:
+// how long they wait (ticks), and which launch from now (0: none) the host takes
+// as late although it ended.
+void resident_limits(pcg_ctx_s* c, long long wait, int drop);
 
 // A claim on CUs of a device for the time of a persistent launch: its
 // work-groups wait for each other, so two such launches of this process may

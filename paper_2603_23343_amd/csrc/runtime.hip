@@ -133,6 +133,8 @@ struct pcg_ctx_s {
     size_t res_bytes = 0;
     ResOut* hres_out = nullptr;  // pinned, behind hres
     uint32_t res_next = 1;
+    long long res_wait = RES_WAIT_TICKS;
+    int res_drop = 0;  // tests: the launch of this number from now counts as late
     // operator: constant coefficients unless pcg_set_coefficients gave k
     const float* kc = nullptr;  // caller's cell coefficients (device, FP32)
     void* dinv = nullptr;       // inverse Jacobi diagonal (storage type), owned
@@ -446,12 +448,12 @@ pcg_status run_resident(pcg_ctx c, ResTask& a, bool copy_state, bool* ran) {
     a.base = c->res_next;
     a.out = reinterpret_cast<ResOut*>(mem);
     a.timing = c->opt.kernel_timing;
-    a.wait = RES_WAIT_TICKS;
+    a.wait = c->res_wait;
     HIPCHK(launch_pcg_resident(c->dt, c->opt.x_accum, c->res_plan, a, st));
     if (copy_state) HIPCHK(hipMemcpyAsync(&c->hst[1], c->st, sizeof(SolveState), hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(c->hres_out, mem, sizeof(ResOut), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    if (c->hres_out->timeout) {
+    if (c->hres_out->timeout || (c->res_drop > 0 && --c->res_drop == 0)) {
         c->res_timeout = true;
         return PCG_OK;
     }
@@ -492,13 +494,30 @@ pcg_status run_iterations(pcg_ctx c, const void* b, const void* x0, int x0_dt, d
     const bool on_chip = allow_resident && c->res_ok && !c->res_timeout;
     if (on_chip) {
         bool ran = false;
+        // A restart iterates the accumulator in place, and a launch that ends
+        // late leaves it part old, part new: the directions' buffers, unused on
+        // the chip, keep the start for the other forms (8 bytes per point).
+        const size_t pb = (size_t)c->n * dt_size(c->dt), xb = (size_t)c->n * sizeof(double);
+        const bool keep = x0 == c->xacc;
+        auto halves = [&](bool save) -> hipError_t {
+            char* const xa = static_cast<char*>(c->xacc);
+            hipError_t e = hipSuccess;
+            for (size_t off = 0, i = 0; off < xb && e == hipSuccess; off += pb, ++i)
+                e = save ? hipMemcpyAsync(c->p[i], xa + off, pb, hipMemcpyDeviceToDevice, st)
+                         : hipMemcpyAsync(xa + off, c->p[i], pb, hipMemcpyDeviceToDevice, st);
+            return e;
+        };
+        if (keep) HIPCHK(halves(true));
         ResTask a{};
         a.r = c->r;
         a.x = c->xacc;
         a.st = c->st;
         s = run_resident(c, a, true, &ran);
         if (s != PCG_OK) return s;
-        if (!ran) return run_iterations(c, b, x0, x0_dt, rtol, maxit, stag, out, false);
+        if (!ran) {
+            if (keep) HIPCHK(halves(false));
+            return run_iterations(c, b, x0, x0_dt, rtol, maxit, stag, out, false);
+        }
         out->fin = c->hst[1];
         out->k1_ms = 1e-5 * (double)c->hres_out->ticks1;
         out->k2_ms = 1e-5 * (double)c->hres_out->ticks2;
@@ -1609,3 +1628,12 @@ pcg_status pcg_get_history(pcg_ctx c, double* hist, int n, int* count) {
 }
 
 }  // extern "C"
+
+namespace pcgmi {
+
+void resident_limits(pcg_ctx c, long long wait, int drop) {
+    c->res_wait = wait;
+    c->res_drop = drop;
+}
+
+}  // namespace pcgmi
