@@ -89,7 +89,11 @@ typedef struct {
                           on the way), use_graph,
                           chunk_iters and x_defer change nothing, and solves of one process
                           take turns on a device once their work-groups would exceed its
-                          CUs */
+                          CUs (first come, first served; after 30 s of waiting a solve
+                          takes another form). Where its work-groups do not come together
+                          within 1 s (another process on the device, a stream without all
+                          CUs) the solve starts over in another form, and the chip is tried
+                          again after a hundred times the time lost; pcg_get_form tells */
     int zchunk_update;  /* z planes per work-group of the two-kernel form's update kernel
                           when it adds to x (every second iteration with x_defer = 1; the
                           other updates take the direction kernel's plan):
@@ -424,7 +428,11 @@ pcg_status pcg_make_pairs(pcg_ctx ctx, int npairs, const double *r_snaps, const 
  * out contiguously, C-order [nz][ny][nx], at its offset in two caller-owned
  * DEVICE arenas: b (FP32) and x (FP64), each of `total` elements
  * (pcg_batch_layout). A batch launch waits for other launches of this process
- * that need their work-groups together (pcg_solve on the chip, other batches).
+ * that need their work-groups together (pcg_solve on the chip, other batches),
+ * 30 s at most; solves on the chip that come later wait for it. On the chip a
+ * work-group waits at most 1 s plus 20 us per problem and iteration of maxit
+ * (30 s at most) for the others; then the streaming kernel starts over, and the
+ * chip is tried again after a hundred times the time lost (pcg_batch_get_form).
  *
  * In the streaming form every problem's r, p and x live in arenas whose rows are padded
  * to a multiple of 4 points (padding held at 0), so 4-wide vector tiles work

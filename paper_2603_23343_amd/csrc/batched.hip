@@ -458,7 +458,8 @@ struct BatchImpl {
     int* d_res_first = nullptr;
     ResOut* h_res_out = nullptr;          // pinned
     ResBatchTask* h_res_tasks = nullptr;  // pinned
-    uint32_t res_next = 1;
+    int res_zero = 0;  // words from the start of res_mem that a launch's results and slots take
+    ResSeries res_series;
 };
 
 namespace {
@@ -792,6 +793,15 @@ bool res_schedule(const BatchImpl& B, int nwg, ResSchedule* out) {
     return true;
 }
 
+// Zeroes the results and slots (numbers start over).
+hipError_t res_zero(BatchImpl& B) {
+    hipLaunchKernelGGL(k_fill_u32, dim3((B.res_zero + 255) / 256), dim3(256), 0, B.stream,
+                       reinterpret_cast<unsigned*>(B.res_mem), B.res_zero, 0u);
+    const hipError_t e = hipGetLastError();
+    if (e == hipSuccess) B.res_series.zeroed();
+    return e;
+}
+
 // Plan and workspace of the on-chip form; without either the streaming kernel
 // serves the batch.
 void res_prepare(BatchImpl& B) try {
@@ -853,10 +863,8 @@ void res_prepare(BatchImpl& B) try {
         q += pad((size_t)2 * sc.plans[i].geo.G * sc.plans[i].S * 4);
     }
     B.res_nwg = nwg;
-    const int nz = (int)((out_b + slots_b) / 4);
-    hipLaunchKernelGGL(k_fill_u32, dim3((nz + 255) / 256), dim3(256), 0, B.stream,
-                       reinterpret_cast<unsigned*>(B.res_mem), nz, 0u);
-    if (hipGetLastError() != hipSuccess) return;
+    B.res_zero = (int)((out_b + slots_b) / 4);
+    if (res_zero(B) != hipSuccess) return;
     if (hipMemcpyAsync(B.d_res_work, work.data(), sizeof(int2) * work.size(), hipMemcpyHostToDevice, B.stream) !=
         hipSuccess)
         return;
@@ -876,7 +884,10 @@ pcg_status res_solve(BatchImpl& B, const float* b, double* x, double rtol2, int 
     // a work-group may wait for others to finish earlier problems: at most
     // all problems' iterations at 20 us, but no more than 30 s
     const double work_s = std::min(30.0, 20e-6 * (double)B.nprob * maxit);
-    const long long wait = RES_WAIT_TICKS + (long long)(1e8 * work_s);
+    ResSeries& rs = B.res_series;
+    const long long wait = rs.wait >= 0 ? rs.wait : RES_WAIT_TICKS + (long long)(1e8 * work_s);
+    const auto t0 = std::chrono::steady_clock::now();
+    if (rs.stale()) BCHK(res_zero(B));
     for (int i = 0; i < B.nprob; ++i) {
         ResBatchTask t = B.res_tasks[i];
         ResTask& a = t.task;
@@ -884,7 +895,7 @@ pcg_status res_solve(BatchImpl& B, const float* b, double* x, double rtol2, int 
         a.r2 = B.r + B.probs[i].ioff;
         a.x = x + B.probs[i].off;
         a.rtol2 = rtol2;
-        a.base = B.res_next;
+        a.base = rs.next;
         a.judge = 1;
         a.maxit = std::max(maxit, 1);  // the streaming form runs at least one iteration, too
         a.max_restarts = B.max_restarts;
@@ -893,22 +904,20 @@ pcg_status res_solve(BatchImpl& B, const float* b, double* x, double rtol2, int 
         B.h_res_tasks[i] = t;
     }
     BCHK(hipMemcpyAsync(B.d_res_tasks, B.h_res_tasks, sizeof(ResBatchTask) * B.nprob, hipMemcpyHostToDevice, B.stream));
+    rs.clean = false;  // until the launch has ended, and ended well
     BCHK(launch_batch_resident(B.d_res_tasks, B.d_res_work, B.d_res_first, B.res_nwg, B.res_lds, B.stream));
     BCHK(hipMemcpyAsync(B.h_res_out, B.res_mem, sizeof(ResOut) * B.nprob, hipMemcpyDeviceToHost, B.stream));
     BCHK(hipStreamSynchronize(B.stream));
     uint32_t used = 0;
+    bool late = false;
     for (int i = 0; i < B.nprob; ++i) {
         const ResOut& o = B.h_res_out[i];
-        if (o.timeout) {
-            B.res_ok = false;  // not tried again
-            return PCG_OK;
-        }
+        late = late || o.timeout;
         used = std::max(used, o.used);
         B.h_out[i] = BatchOut{o.iters, o.done, o.restarts, B.force_agent ? 0 : 1, o.rr, o.rr0, o.rr_true,
                               (unsigned long long)o.t_begin, (unsigned long long)o.t_done};
     }
-    B.res_next += used + 1;
-    *ran = true;
+    *ran = rs.ended(late, used, t0);
     return PCG_OK;
 }
 
@@ -1217,7 +1226,7 @@ pcg_status pcg_batch_solve(pcg_batch bt, const float* b, double* x, double rtol,
     // problem may be solved in place there.
     const uintptr_t b0 = reinterpret_cast<uintptr_t>(b), x0 = reinterpret_cast<uintptr_t>(x);
     const bool apart = b0 + (size_t)B.total * sizeof(float) <= x0 || x0 + (size_t)B.total * sizeof(double) <= b0;
-    if (B.res_ok && hold.ok() && apart) {
+    if (B.res_ok && B.res_series.ready() && hold.ok() && apart) {
         const pcg_status st = res_solve(B, b, x, rtol2, maxit, &on_chip);
         if (st != PCG_OK) return st;
     }
@@ -1291,3 +1300,13 @@ pcg_status pcg_batch_solve(pcg_batch bt, const float* b, double* x, double rtol,
 }
 
 }  // extern "C"
+
+namespace pcgmi {
+
+void batch_limits(pcg_batch bt, long long wait, int drop) {
+    bt->impl.res_series.wait = wait;
+    bt->impl.res_series.drop = drop;
+}
+void batch_retry(pcg_batch bt) { bt->impl.res_series.again = {}; }
+
+}  // namespace pcgmi

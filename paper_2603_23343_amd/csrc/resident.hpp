@@ -1,11 +1,13 @@
 // resident.hpp -- host interface of the on-chip PCG (resident.hip).
 #pragma once
 
+#include <chrono>
 #include <utility>
 
 #include "internal.hpp"
 
 struct pcg_ctx_s;
+struct pcg_batch_s;
 
 namespace pcgmi {
 
@@ -56,7 +58,7 @@ struct ResPlan {
 
 // Result of a launch (work-group 0), all but the first field.
 struct ResOut {
-    int timeout;     // a wait ran out: the solve did not finish (set once, never cleared)
+    int timeout;     // a wait ran out: the solve did not finish (the host zeroes it before the next launch)
     int done;        // as SolveState::done
     int iters;       // iterations, restarts included
     int last_iters;  // iterations since the last restart
@@ -103,6 +105,39 @@ struct ResTask {
     long long wait;  // ticks (10 ns) a work-group waits in a grid sum at most
 };
 constexpr long long RES_WAIT_TICKS = 100000000;  // 1 s
+
+// What a context or a batch knows of its launches: the sums' numbers that are
+// used up, whether the slots can be trusted, and when to try again after a
+// launch whose work-groups did not come together (another process on the
+// device, a stream without all CUs): a hundred times what the attempt lost, so
+// that a lasting interference costs a hundredth and a passing one ends.
+struct ResSeries {
+    uint32_t next = 1;
+    bool clean = true;  // false: slots and result must be zeroed first
+    long long wait = -1;  // tests: limit of a wait in ticks (-1: the form's own)
+    int drop = 0;         // tests: the launch of this number from now counts as late
+    std::chrono::steady_clock::time_point again{};
+
+    bool ready() const { return std::chrono::steady_clock::now() >= again; }
+    // Zeroing is due: a launch did not end well, or the numbers near their end.
+    bool stale() const { return !clean || next > (1u << 30); }
+    void zeroed() {
+        next = 1;
+        clean = true;
+    }
+    // The end of a launch that began at t0; true if its results count.
+    bool ended(bool timeout, uint32_t used, std::chrono::steady_clock::time_point t0) {
+        const bool late = timeout || (drop > 0 && --drop == 0);
+        if (late) {
+            const auto now = std::chrono::steady_clock::now();
+            again = now + 100 * (now - t0);
+        } else {
+            next += used + 1;
+            clean = true;
+        }
+        return !late;
+    }
+};
 // How long a launch waits for its CUs on the host at most (results would
 // otherwise depend on what else runs: the other forms sum in another order).
 constexpr double RES_HOLD_S = 30.0;
@@ -129,10 +164,12 @@ hipError_t launch_resident_f32(const ResPlan& p, const ResTask& a, hipStream_t s
 hipError_t launch_resident_f32_var(const ResPlan& p, const ResTask& a, hipStream_t s);
 hipError_t launch_resident_f64(const ResPlan& p, const ResTask& a, hipStream_t s);
 
-// For tests of what follows a launch whose work-groups did not come together:
-// how long they wait (ticks), and which launch from now (0: none) the host takes
-// as late although it ended.
+// For tests of what follows a launch whose work-groups did not come together
+// (ResSeries::wait, drop); after a retry the next solve tries again at once.
 void resident_limits(pcg_ctx_s* c, long long wait, int drop);
+void resident_retry(pcg_ctx_s* c);
+void batch_limits(pcg_batch_s* b, long long wait, int drop);
+void batch_retry(pcg_batch_s* b);
 
 // A claim on CUs of a device for the time of a persistent launch: its
 // work-groups wait for each other, so two such launches of this process may

@@ -124,17 +124,15 @@ struct pcg_ctx_s {
     int last_iters = 0;
     int form = PCG_FORM_NONE;  // of the last Jacobi-PCG iterations
     // on-chip form (resident_kernel.hpp): plan for the current operator,
-    // exchange buffers (zeroed once; sums are numbered, never reused)
+    // exchange buffers (zeroed once and after a launch that did not end; sums
+    // are numbered, never reused)
     int dev = 0, cus = 0;
     bool res_ok = false;       // the grid fits and the options leave the form open
-    bool res_timeout = false;  // a launch could not get its work-groups together: not tried again
     ResPlan res_plan{};
     void* res_mem = nullptr;  // ResOut (256 bytes), the slots, the surfaces
     size_t res_bytes = 0;
     ResOut* hres_out = nullptr;  // pinned, behind hres
-    uint32_t res_next = 1;
-    long long res_wait = RES_WAIT_TICKS;
-    int res_drop = 0;  // tests: the launch of this number from now counts as late
+    ResSeries res_series;
     // operator: constant coefficients unless pcg_set_coefficients gave k
     const float* kc = nullptr;  // caller's cell coefficients (device, FP32)
     void* dinv = nullptr;       // inverse Jacobi diagonal (storage type), owned
@@ -425,6 +423,7 @@ void plan_resident(pcg_ctx c) {
         }
         if (launch_zero(DT_F64, (RES_HEAD_BYTES + RES_SLOT_BYTES) / 8, c->res_mem, c->stream) != hipSuccess) return;
         c->res_bytes = need;
+        c->res_series.zeroed();
     }
     c->res_ok = true;
 }
@@ -439,26 +438,28 @@ pcg_status run_resident(pcg_ctx c, ResTask& a, bool copy_state, bool* ran) {
     if (!hold.ok()) return PCG_OK;
     hipStream_t st = c->stream;
     char* const mem = static_cast<char*>(c->res_mem);
+    ResSeries& rs = c->res_series;
+    const auto t0 = std::chrono::steady_clock::now();
+    if (rs.stale()) {
+        HIPCHK(launch_zero(DT_F64, (RES_HEAD_BYTES + RES_SLOT_BYTES) / 8, mem, st));
+        rs.zeroed();
+    }
     a.geo = c->res_plan.geo;
     a.kc = c->kc;
     a.dinv = op_of(c).dinv;
     a.hist = c->hist;
     a.slots = mem + RES_HEAD_BYTES;
     a.surf = mem + RES_HEAD_BYTES + RES_SLOT_BYTES;
-    a.base = c->res_next;
+    a.base = rs.next;
     a.out = reinterpret_cast<ResOut*>(mem);
     a.timing = c->opt.kernel_timing;
-    a.wait = c->res_wait;
+    a.wait = rs.wait >= 0 ? rs.wait : RES_WAIT_TICKS;
+    rs.clean = false;  // until the launch has ended, and ended well
     HIPCHK(launch_pcg_resident(c->dt, c->opt.x_accum, c->res_plan, a, st));
     if (copy_state) HIPCHK(hipMemcpyAsync(&c->hst[1], c->st, sizeof(SolveState), hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(c->hres_out, mem, sizeof(ResOut), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    if (c->hres_out->timeout || (c->res_drop > 0 && --c->res_drop == 0)) {
-        c->res_timeout = true;
-        return PCG_OK;
-    }
-    c->res_next += c->hres_out->used + 1;
-    *ran = true;
+    *ran = rs.ended(c->hres_out->timeout != 0, c->hres_out->used, t0);
     return PCG_OK;
 }
 
@@ -491,7 +492,7 @@ pcg_status run_iterations(pcg_ctx c, const void* b, const void* x0, int x0_dt, d
         HIPCHK(launch_pcg_start_zero(c->dt, c->n, b, c->r, c->xacc, xacc_dt, c->p[0], op_of(c).dinv, c->st,
                                      c->hist, red_of(c), st));
     }
-    const bool on_chip = allow_resident && c->res_ok && !c->res_timeout;
+    const bool on_chip = allow_resident && c->res_ok && c->res_series.ready();
     if (on_chip) {
         bool ran = false;
         // A restart iterates the accumulator in place, and a launch that ends
@@ -1019,7 +1020,7 @@ pcg_status pcg_solve(pcg_ctx c, const void* b, void* x, double rtol, int maxit, 
     const void* x0 = c->opt.use_x0 ? x : nullptr;
     int x0_dt = c->opt.x_dtype;
     bool solved = false;
-    if (c->res_ok && !c->res_timeout && !x0 && c->opt.x_dtype == DT_F64) {
+    if (c->res_ok && c->res_series.ready() && !x0 && c->opt.x_dtype == DT_F64) {
         // on the chip, start, FP64 judge and restarts included
         Range r("PCG on the chip");
         pcg_status s = ensure_hist(c, maxit);
@@ -1632,8 +1633,9 @@ pcg_status pcg_get_history(pcg_ctx c, double* hist, int n, int* count) {
 namespace pcgmi {
 
 void resident_limits(pcg_ctx c, long long wait, int drop) {
-    c->res_wait = wait;
-    c->res_drop = drop;
+    c->res_series.wait = wait;
+    c->res_series.drop = drop;
 }
+void resident_retry(pcg_ctx c) { c->res_series.again = {}; }
 
 }  // namespace pcgmi
