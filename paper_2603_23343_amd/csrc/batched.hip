@@ -1219,6 +1219,7 @@ pcg_status pcg_batch_solve(pcg_batch bt, const float* b, double* x, double rtol,
     BatchImpl& B = bt->impl;
     const auto t0 = std::chrono::steady_clock::now();
     const double rtol2 = rtol * rtol;
+    BCHK(hipStreamSynchronize(B.stream));  // no claim is held while earlier work runs
     CuHold hold(B.dev, B.cus, B.cus, RES_HOLD_S);
     bool on_chip = false;
     // On the chip x is written before its residual is formed from b. The

@@ -16,6 +16,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <optional>
 #include <string>
 #include <vector>
 
@@ -428,14 +429,23 @@ void plan_resident(pcg_ctx c) {
     c->res_ok = true;
 }
 
-// Launch a task on the chip and wait for its result (c->hres_out; with
-// copy_state also c->hst[1]). *ran is false when its work-groups could not be
-// brought together: the task's outputs may then hold a mix of its start and
-// its end, and the caller starts over in another form.
+// Claims the CUs of the context's plan for a launch. The stream's earlier work
+// is waited for first: a claim held meanwhile would keep other solves off CUs
+// that are not used yet, and if that work waits for one of them, for as long
+// as they wait for a claim.
+pcg_status claim_cus(pcg_ctx c, std::optional<CuHold>& hold) {
+    HIPCHK(hipStreamSynchronize(c->stream));
+    hold.emplace(c->dev, c->res_plan.geo.G, c->cus, RES_HOLD_S);
+    if (!hold->ok()) hold.reset();
+    return PCG_OK;
+}
+
+// Launch a task on the chip (under a claim) and wait for its result
+// (c->hres_out; with copy_state also c->hst[1]). *ran is false when its
+// work-groups could not be brought together: the task's outputs may then hold a
+// mix of its start and its end, and the caller starts over in another form.
 pcg_status run_resident(pcg_ctx c, ResTask& a, bool copy_state, bool* ran) {
     *ran = false;
-    CuHold hold(c->dev, c->res_plan.geo.G, c->cus, RES_HOLD_S);
-    if (!hold.ok()) return PCG_OK;
     hipStream_t st = c->stream;
     char* const mem = static_cast<char*>(c->res_mem);
     ResSeries& rs = c->res_series;
@@ -473,6 +483,11 @@ pcg_status run_iterations(pcg_ctx c, const void* b, const void* x0, int x0_dt, d
     if (s != PCG_OK) return s;
     hipStream_t st = c->stream;
     const int xacc_dt = c->opt.x_accum;
+    std::optional<CuHold> hold;
+    if (allow_resident && c->res_ok && c->res_series.ready()) {
+        s = claim_cus(c, hold);
+        if (s != PCG_OK) return s;
+    }
 
     // Host-side initial state: rtol^2 (scaled by ||b||^2 on the device), 1/6, maxit.
     SolveState init{};
@@ -492,8 +507,7 @@ pcg_status run_iterations(pcg_ctx c, const void* b, const void* x0, int x0_dt, d
         HIPCHK(launch_pcg_start_zero(c->dt, c->n, b, c->r, c->xacc, xacc_dt, c->p[0], op_of(c).dinv, c->st,
                                      c->hist, red_of(c), st));
     }
-    const bool on_chip = allow_resident && c->res_ok && c->res_series.ready();
-    if (on_chip) {
+    if (hold) {
         bool ran = false;
         // A restart iterates the accumulator in place, and a launch that ends
         // late leaves it part old, part new: the directions' buffers, unused on
@@ -516,6 +530,7 @@ pcg_status run_iterations(pcg_ctx c, const void* b, const void* x0, int x0_dt, d
         s = run_resident(c, a, true, &ran);
         if (s != PCG_OK) return s;
         if (!ran) {
+            hold.reset();
             if (keep) HIPCHK(halves(false));
             return run_iterations(c, b, x0, x0_dt, rtol, maxit, stag, out, false);
         }
@@ -1025,6 +1040,9 @@ pcg_status pcg_solve(pcg_ctx c, const void* b, void* x, double rtol, int maxit, 
         Range r("PCG on the chip");
         pcg_status s = ensure_hist(c, maxit);
         if (s != PCG_OK) return s;
+        std::optional<CuHold> hold;
+        s = claim_cus(c, hold);
+        if (s != PCG_OK) return s;
         ResTask a{};
         a.r = b;
         a.r2 = c->r;
@@ -1033,7 +1051,7 @@ pcg_status pcg_solve(pcg_ctx c, const void* b, void* x, double rtol, int maxit, 
         a.judge = 1;
         a.maxit = maxit;
         a.max_restarts = c->opt.max_restarts;
-        s = run_resident(c, a, false, &solved);
+        if (hold) s = run_resident(c, a, false, &solved);
         if (s != PCG_OK) return s;
         if (solved) {
             const ResOut& o = *c->hres_out;
