@@ -725,7 +725,6 @@ struct ResSchedule {
 
 bool res_schedule(const BatchImpl& B, int nwg, ResSchedule* out) {
     const int np = B.nprob;
-    const int nshape = (int)(sizeof RES_SHAPES / sizeof RES_SHAPES[0]);
     struct Cand {
         ResPlan p;
         int shape;
@@ -734,8 +733,8 @@ bool res_schedule(const BatchImpl& B, int nwg, ResSchedule* out) {
     std::vector<std::vector<Cand>> cands(np);
     for (int i = 0; i < np; ++i) {
         const BatchProb& pr = B.probs[i];
-        for (int sh = 0; sh < nshape; ++sh)
-            for (int V : RES_BATCH_VS) {
+        for (int sh = 0; sh < RES_NSHAPES; ++sh)
+            for (int V : res_list(ResBatchVs{})) {
                 ResPlan p;
                 if (!resident_candidate(pr.nx, pr.ny, pr.nz, DT_F32, false, RES_SHAPES[sh][0], RES_SHAPES[sh][1], V,
                                         nwg, &p))

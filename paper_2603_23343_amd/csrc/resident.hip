@@ -52,7 +52,7 @@ bool resident_plan(int nx, int ny, int nz, int dt, bool var, int max_wg, ResPlan
     bool have = false;
     double best = 0.0;
     for (const auto& sh : RES_SHAPES)
-        for (int V : RES_VS) {
+        for (int V : res_list(ResVs{})) {
             ResPlan p;
             if (V > most || !resident_candidate(nx, ny, nz, dt, var, sh[0], sh[1], V, max_wg, &p)) continue;
             const double cost = per_v * p.V + 0.017 * p.geo.G;

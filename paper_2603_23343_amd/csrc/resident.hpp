@@ -1,6 +1,7 @@
 // resident.hpp -- host interface of the on-chip PCG (resident.hip).
 #pragma once
 
+#include <array>
 #include <chrono>
 #include <utility>
 
@@ -19,8 +20,9 @@ constexpr size_t RES_HALO_LDS = (size_t)4 * 512 * 4;  // grid indices of the hal
 // Compiled work-group shapes (log2 of the threads along x and y; 512 in all)
 // and z points per thread.
 constexpr int RES_SHAPES[][2] = {{5, 4}, {4, 4}, {3, 4}};
+constexpr int RES_NSHAPES = sizeof RES_SHAPES / sizeof RES_SHAPES[0];
 using ResVs = std::integer_sequence<int, 2, 4, 6, 8, 10, 12, 16, 20, 24, 28, 32>;
-constexpr int RES_VS[] = {2, 4, 6, 8, 10, 12, 16, 20, 24, 28, 32};
+template <int... V> constexpr std::array<int, sizeof...(V)> res_list(std::integer_sequence<int, V...>) { return {V...}; }
 // Points per thread that the 256 registers of a lane hold: r, p, q and x, or
 // r, p, q, five face coefficients and D^-1 (x then lies in LDS).
 constexpr int res_most_v(bool f64, bool var) { return f64 ? (var ? 8 : 16) : (var ? 16 : 32); }
@@ -153,8 +155,8 @@ struct ResBatchTask {
 // this order, which is the same order of problems for all of them.
 hipError_t launch_batch_resident(const ResBatchTask* tasks, const int2* work, const int* first, int nwg, size_t lds,
                                  hipStream_t s);
-// Points per thread compiled for batches.
-constexpr int RES_BATCH_VS[] = {4, 8, 12, 16, 24, 32};
+// Points per thread compiled for batches (the kernel's bodies follow this list).
+using ResBatchVs = std::integer_sequence<int, 4, 8, 12, 16, 24, 32>;
 
 bool resident_candidate(int nx, int ny, int nz, int dt, bool var, int lx, int ly, int V, int max_wg, ResPlan* out);
 // A plan for the grid on at most max_wg work-groups; false if it does not fit.

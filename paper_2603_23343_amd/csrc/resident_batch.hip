@@ -18,17 +18,17 @@ __global__ void __launch_bounds__(resident::RT, 2) k_batch_resident(const ResBat
         const ResTask& a = tasks[w.x].task;
         const int code = tasks[w.x].shape * 64 + tasks[w.x].V;
         bool ok = false;
-        auto run = [&]<int V>() {
-            if (code == V) ok = resident::solve_box<float, double, V, false, 5, 4>(a, w.y, dyn, L);
-            if (code == 64 + V) ok = resident::solve_box<float, double, V, false, 4, 4>(a, w.y, dyn, L);
-            if (code == 128 + V) ok = resident::solve_box<float, double, V, false, 3, 4>(a, w.y, dyn, L);
+        // every body inlined: called ones would each need the caller's registers saved
+        auto one = [&]<int V, int SH>() __attribute__((always_inline)) {
+            if (code == SH * 64 + V)
+                ok = resident::solve_box<float, double, V, false, RES_SHAPES[SH][0], RES_SHAPES[SH][1]>(a, w.y, dyn, L);
         };
-        run.template operator()<4>();
-        run.template operator()<8>();
-        run.template operator()<12>();
-        run.template operator()<16>();
-        run.template operator()<24>();
-        run.template operator()<32>();
+        auto run = [&]<int V, int... SH>(std::integer_sequence<int, SH...>) __attribute__((always_inline)) {
+            (one.template operator()<V, SH>(), ...);
+        };
+        [&]<int... V>(std::integer_sequence<int, V...>) __attribute__((always_inline)) {
+            (run.template operator()<V>(std::make_integer_sequence<int, RES_NSHAPES>{}), ...);
+        }(ResBatchVs{});
         if (!ok) return;  // the others' waits run out too
         __syncthreads();
     }

@@ -856,11 +856,15 @@ template <typename T, typename X, bool VAR, int LX, int LY> hipError_t pick_v(co
 }
 
 template <typename T, typename X, bool VAR> hipError_t pick_shape(const ResPlan& p, const ResTask& a, hipStream_t s) {
-    const int lx = p.geo.lx, ly = p.geo.ly;
-    if (lx == 5 && ly == 4) return pick_v<T, X, VAR, 5, 4>(p, a, s);
-    if (lx == 4 && ly == 4) return pick_v<T, X, VAR, 4, 4>(p, a, s);
-    if (lx == 3 && ly == 4) return pick_v<T, X, VAR, 3, 4>(p, a, s);
-    return hipErrorInvalidValue;
+    hipError_t e = hipErrorInvalidValue;
+    auto one = [&]<int SH>() {
+        constexpr int LX = RES_SHAPES[SH][0], LY = RES_SHAPES[SH][1];
+        if (p.geo.lx == LX && p.geo.ly == LY) e = pick_v<T, X, VAR, LX, LY>(p, a, s);
+    };
+    [&]<int... SH>(std::integer_sequence<int, SH...>) {
+        (one.template operator()<SH>(), ...);
+    }(std::make_integer_sequence<int, RES_NSHAPES>{});
+    return e;
 }
 
 }  // namespace resident
