@@ -251,6 +251,16 @@ __device__ __forceinline__ int scale_of(double rr, double n) {
 __device__ __forceinline__ float times_2(float v, int e) { return __builtin_amdgcn_ldexpf(v, e); }
 __device__ __forceinline__ double times_2(double v, int e) { return __builtin_amdgcn_ldexp(v, e); }
 
+// The thread's index, formed anew: what is derived from it is computed where
+// it is used. Addresses kept over an iteration, or hoisted out of it, are
+// spilled, and a reload among the surface stores waits until the stores before
+// it have arrived.
+__device__ __forceinline__ int fresh_thread() {
+    int u = threadIdx.x;
+    __asm__ volatile("" : "+v"(u));
+    return u;
+}
+
 // Face coefficients of a thread's points (variable operator), computed once.
 template <typename C, int V, bool VAR> struct Faces {
     C l[V], r[V], d[V], u[V], z[V + 1];
@@ -327,8 +337,7 @@ __device__ __forceinline__ bool solve_box(const ResTask& a, const int rank, unsi
         int x, y, z, gi, nv;
     };
     auto own = [&]() {
-        int u = threadIdx.x;
-        __asm__ volatile("" : "+v"(u));
+        const int u = fresh_thread();
         const int ux = u & (TX - 1), uy = (u >> LX) & (TY - 1), uz = (u >> (LX + LY)) * V;
         Own o{ox + ux, oy + uy, oz + uz, 0, 0};
         o.gi = (o.z * g.ny + o.y) * g.nx + o.x;
@@ -461,6 +470,7 @@ __device__ __forceinline__ bool solve_box(const ResTask& a, const int rank, unsi
     // The box's surface values of q: V values along z per thread on the x and
     // y faces (16-byte stores), one on the z faces (qt: the thread's topmost).
     auto publish = [&](const int mine, const C qt) {
+        const int u = fresh_thread(), tx = u & (TX - 1), ty = (u >> LX) & (TY - 1), z0 = (u >> (LX + LY)) * V;
         if (tx == 0 && hxl) put_run<C, V>(surf, mine + (ty * ZP + z0) * (int)sizeof(C), q);
         if (tx == ex - 1 && hxr) put_run<C, V>(surf, mine + (NXF + ty * ZP + z0) * (int)sizeof(C), q);
         if (ty == 0 && hyl) put_run<C, V>(surf, mine + (2 * NXF + tx * ZP + z0) * (int)sizeof(C), q);
@@ -515,9 +525,8 @@ __device__ __forceinline__ bool solve_box(const ResTask& a, const int rank, unsi
             rr0 = rr = uniform(times_2(tot[0], 2 * scale));
             tol2 = uniform(a.rtol2 * rr0);
             rho = VAR ? uniform(times_2(tot[NB - 1], 2 * scale)) : uniform(dconst * rr0);
-            rr_true = rr0;
             if (!isfinite(rr0)) done = 2;
-            else if (rr0 == 0.0 || (rr <= tol2 && !a.step_first)) done = 1;
+            else if (rr <= (a.step_first ? 0.0 : tol2)) done = 1;
             else if (maxit <= 0) done = 3;
             if (keeper && hist) hist[0] = rr;
         }
@@ -770,7 +779,7 @@ __device__ __forceinline__ bool solve_box(const ResTask& a, const int rank, unsi
         beta_d = 0.0;
         iters = seg0 = 0;
         maxit = a.maxit - total;
-        done = !isfinite(rr) ? 2 : rr == 0.0 || (rr <= tol2 && !a.step_first) ? 1 : 0;
+        done = !isfinite(rr) ? 2 : rr <= (a.step_first ? 0.0 : tol2) ? 1 : 0;
         if (keeper && hist) hist[0] = rr;
     }
     if (late) {
