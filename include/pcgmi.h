@@ -428,8 +428,8 @@ pcg_status pcg_make_pairs(pcg_ctx ctx, int npairs, const double *r_snaps, const 
  * out contiguously, C-order [nz][ny][nx], at its offset in two caller-owned
  * DEVICE arenas: b (FP32) and x (FP64), each of `total` elements
  * (pcg_batch_layout). A batch launch waits for other launches of this process
- * that need their work-groups together (pcg_solve on the chip, other batches),
- * 30 s at most; solves on the chip that come later wait for it. On the chip a
+ * that need their work-groups together (pcg_solve on the chip, other batches);
+ * solves on the chip that come later wait for it. On the chip a
  * work-group waits at most 1 s plus 20 us per problem and iteration of maxit
  * (30 s at most) for the others; then the streaming kernel starts over, and the
  * chip is tried again after a hundred times the time lost (pcg_batch_get_form).

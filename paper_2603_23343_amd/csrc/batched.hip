@@ -697,9 +697,8 @@ pcg_status upload_plans(BatchImpl& B) {
 
 // Run the whole batch eagerly and read back per-problem results.
 pcg_status run_once(BatchImpl& B, const float* b, double* x, double rtol2, int maxit, int* herr) {
-    // The launch fills the device, so it claims every CU; without the claim it
-    // starts anyway and its own barrier bound decides.
-    CuHold hold(B.dev, B.cus, B.cus, RES_HOLD_S);
+    // The launch fills the device, so it claims every CU.
+    CuHold hold(B.dev, B.cus, B.cus, RES_HOLD_BATCH_S);
     BCHK(enqueue_batch(B, b, x, rtol2, maxit, B.stream));
     BCHK(hipMemcpyAsync(B.h_out, B.out, sizeof(BatchOut) * B.nprob, hipMemcpyDeviceToHost, B.stream));
     BCHK(hipMemcpyAsync(herr, B.err, sizeof(int), hipMemcpyDeviceToHost, B.stream));
@@ -1219,7 +1218,7 @@ pcg_status pcg_batch_solve(pcg_batch bt, const float* b, double* x, double rtol,
     const auto t0 = std::chrono::steady_clock::now();
     const double rtol2 = rtol * rtol;
     BCHK(hipStreamSynchronize(B.stream));  // no claim is held while earlier work runs
-    CuHold hold(B.dev, B.cus, B.cus, RES_HOLD_S);
+    CuHold hold(B.dev, B.cus, B.cus, RES_HOLD_BATCH_S);
     bool on_chip = false;
     // On the chip x is written before its residual is formed from b. The
     // streaming form copies b at its start and writes x last, so a batch of one

@@ -143,6 +143,10 @@ struct ResSeries {
 // How long a launch waits for its CUs on the host at most (results would
 // otherwise depend on what else runs: the other forms sum in another order).
 constexpr double RES_HOLD_S = 30.0;
+// A batch waits as long as it takes: its streaming kernel needs its
+// work-groups together, too, and beside a launch that holds CUs its barriers
+// would run out of time. Every claim ends, since every wait of its holder does.
+constexpr double RES_HOLD_BATCH_S = 1e8;
 
 // One problem of a batch: its task and its compiled shape.
 struct ResBatchTask {
