@@ -82,8 +82,9 @@ typedef struct {
                           PCG, the same iterates in exact arithmetic; moves 48 instead of
                           40 bytes per point); -1 = default: on the chip where the grid
                           fits (F32 or F64 storage, FP64 x accumulator, no tile or zchunk
-                          given; up to about 4 M points in F32, half of that in F64 or with
-                          cell coefficients), else chosen by grid size. On the chip the
+                          given; 160^3 points in F32, 128^3 in F64 or with cell
+                          coefficients; fewer where a grid is flat in z, which alone is
+                          split within a thread), else chosen by grid size. On the chip the
                           iterates are those of 0 (other summation order; a right-hand
                           side whose squares FP32 cannot hold is scaled by a power of two
                           on the way), use_graph,
@@ -415,8 +416,8 @@ pcg_status pcg_make_pairs(pcg_ctx ctx, int npairs, const double *r_snaps, const 
  * x0 = 0) in ONE persistent kernel launch. Batching is not part of the
  * paper's method; the per-problem iteration is the single-problem solver's.
  *
- * Two forms. On the chip (cfgs = NULL, every problem at most about 4 M
- * points): a problem's vectors live in the registers and LDS of its
+ * Two forms. On the chip (cfgs = NULL, every problem fits as in pcg_solve, and
+ * b and x do not overlap): a problem's vectors live in the registers and LDS of its
  * work-groups for all its iterations, as in pcg_solve, and work-groups take
  * problems from lists made at creation. Streaming (otherwise): every
  * work-group of the launch belongs to one problem; a problem's work-groups
@@ -455,7 +456,9 @@ typedef struct pcg_batch_s *pcg_batch;
  * 2 or 5), or NULL to use the cache / the
  * autotuner. cache_path: JSON file read and rewritten by the autotuner (NULL:
  * no cache). tune_iters: iterations per tuning launch (<= 0: 20). Allocates
- * the workspace (3 FP32 and 1 FP64 row-padded arenas, per-problem scalars). PCG_E_UNSUPPORTED if
+ * the workspace of both forms (3 FP32 and 1 FP64 row-padded arenas, per-problem
+ * scalars; box surfaces) and measures the streaming form's shapes also where
+ * solves will run on the chip: it serves where the chip cannot. PCG_E_UNSUPPORTED if
  * more problems than resident work-groups fall on one XCD. */
 pcg_status pcg_batch_create(pcg_batch *out, int nprob, const int *dims, const int *cfgs,
                             const char *cache_path, int tune_iters, void *hip_stream);

@@ -3,7 +3,7 @@
 //
 // Two forms. Where the caller leaves the tiles to the library and every
 // problem fits, the problems are solved on the chip (resident_batch.hip): 64
-// cubes of 16 to 128 points an edge to 1e-8 take 34.1 ms against 61.1 ms, an
+// cubes of 16 to 128 points an edge to 1e-8 take 32.9 ms against 61.1 ms, an
 // iteration moving only box surfaces instead of 34 bytes per point. The rest
 // of this comment is the streaming form, for larger problems and for given
 // tile shapes.

@@ -2,7 +2,8 @@
 //
 // The paper keeps a solve's vectors in the cores' SRAM for all iterations
 // (Sec. VII); MI355X has 128 MiB of vector registers and 40 MiB of LDS, so a
-// grid of up to ~4 M points fits as well. One persistent launch runs every
+// grid of up to ~4 M points fits as well (160^3; flat ones of fewer points may
+// not, since only z is split within a thread). One persistent launch runs every
 // iteration: a work-group owns a box of the grid, r, p, q and the FP64 x of its
 // points live in registers, the current direction p (with a one-point halo)
 // in LDS. Per iteration only scalars and the boxes' surfaces leave a CU.
@@ -19,7 +20,8 @@
 // loads are waited for alone. Published before the first sum and read after
 // it, an iteration on 512 x 112 x 64 took 12.0 us instead of 9.8 (boxes inside
 // the grid have six surfaces to send and the others waited for them), at 128^3
-// with cell coefficients 10.2 instead of 7.6, at 32^3 3.9 instead of 3.6.
+// with cell coefficients 10.2 instead of 7.6, at 32^3 3.9 instead of 3.6 (9.7,
+// 7.4 and 3.6 with the stores' addresses formed where they are used).
 //
 // What bounds an iteration: the two grid sums (1.1 us over 8 work-groups, 2.7
 // over 256), then, in wide boxes, the stencil's five LDS accesses per point
@@ -36,7 +38,7 @@
 // work-group. The work-groups must run at the same time: at most one per CU is
 // launched (the host reserves them, resident.hpp), and every wait is bounded;
 // a work-group that waited too long raises a flag and leaves, and the host
-// runs the solve with the two-kernel form instead.
+// runs the solve in another form instead.
 #pragma once
 
 #include "ops.hpp"

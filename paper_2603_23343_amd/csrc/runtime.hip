@@ -400,12 +400,13 @@ bool want_single_reduction(pcg_ctx c) {
 // iteration form and the tiles to the library, the types are compiled, and
 // the grid fits. The two-kernel form moves 34 bytes per point and iteration
 // through HBM and waits for two kernel boundaries; on the chip an iteration
-// took 3.6 us against 11.5-15 at 32^3, 9.8 against 29 on 512 x 112 x 64 and
-// 7.6 against 40 at 128^3 with cell coefficients (before the surfaces were
+// takes 3.6 us against 11.5-15 at 32^3, 9.7 against 29 on 512 x 112 x 64 and
+// 7.4 against 40 at 128^3 with cell coefficients (before the surfaces were
 // sent during the sums 9.3 against 21 at 128^3 and 11.6 against 41 there in
-// FP64), so it is taken wherever it fits (about 4.1 M FP32 points, half as
-// many in FP64 or with coefficients). Without the
-// workspace the other forms serve.
+// FP64), so it is taken wherever it fits: 160^3 in FP32, 128^3 in FP64 or with
+// coefficients; only z is split within a thread, so flat grids (400 x 400 x 8)
+// need more boxes than there are CUs. Without the workspace the other forms
+// serve.
 void plan_resident(pcg_ctx c) {
     c->res_ok = false;
     const pcg_options& o = c->opt;
