@@ -412,9 +412,14 @@ void plan_resident(pcg_ctx c) {
     const pcg_options& o = c->opt;
     if (o.single_reduction >= 0 || o.tile_x > 0 || o.tile_y > 0 || o.zchunk > 0 || o.zchunk_update != 0) return;
     if ((c->dt != DT_F32 && c->dt != DT_F64) || o.x_accum != DT_F64) return;
-    if (!resident_plan(c->nx, c->ny, c->nz, c->dt, c->kc != nullptr, c->cus, &c->res_plan)) return;
-    const size_t need = RES_HEAD_BYTES + RES_SLOT_BYTES +
-                        (size_t)2 * c->res_plan.geo.G * c->res_plan.S * (c->dt == DT_F64 ? 8 : 4);
+    const bool var = c->kc != nullptr;
+    if (!resident_plan(c->nx, c->ny, c->nz, c->dt, var, c->cus, &c->res_plan)) return;
+    // Room for the other operator's plan as well: coefficients set later then
+    // cost neither an allocation nor the device-wide wait of a free (0.3 ms).
+    ResPlan other{};
+    if (!resident_plan(c->nx, c->ny, c->nz, c->dt, !var, c->cus, &other)) other = c->res_plan;
+    const size_t values = std::max((size_t)c->res_plan.geo.G * c->res_plan.S, (size_t)other.geo.G * other.S);
+    const size_t need = RES_HEAD_BYTES + RES_SLOT_BYTES + 2 * values * (c->dt == DT_F64 ? 8 : 4);
     if (need > c->res_bytes) {
         if (c->res_mem) (void)hipFree(c->res_mem);
         c->res_bytes = 0;

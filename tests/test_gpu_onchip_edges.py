@@ -159,3 +159,18 @@ def test_phase_times_leave_out_the_start(P):
     print("phase 1 of 100:", each, "of 1:", [i["k1_ms"] for i in one], flush=True)
     assert all(i["k1_launches"] == 1 for i in one)
     assert min(i["k1_ms"] for i in one) <= 1.25 * each
+
+
+def test_coefficients_reuse_the_exchange_buffers(P):
+    """The box surfaces' memory is made at creation for either operator: setting
+    coefficients allocates D^-1 (8 MiB here) and nothing else, and frees nothing."""
+    n = 128 ** 3
+    k = torch.ones(n, device="cuda")
+    ctx = P.pcg_create(128, 128, 128, torch.float32, x_dtype=torch.float64)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    P.pcg_set_coefficients(ctx, k)
+    torch.cuda.synchronize()
+    took = free - torch.cuda.mem_get_info()[0]
+    print("setting coefficients took", took, "bytes", flush=True)
+    assert took <= 4 * n
